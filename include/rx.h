@@ -193,7 +193,11 @@ int rx_program_upload(rx_program* prog, void* d_buf, size_t cap, void* stream);
  * d_out[i] is set to 1 if string i is in the language (a substring of it, for
  * RX_SEARCH), else 0.  Runs asynchronously on `stream`; allocates nothing.
  * n == 0 is a no-op.  The kernel variant is chosen from the program's size
- * and the string count: wavefronts per string for sets above 16 words, and
+ * and the string count.  A searched program that does not match the empty
+ * string, with a set of at most 16 words, runs over equal spans of the strings' bytes, one
+ * lane per span of 16, 32 or 64 bytes: every lane follows the matches that
+ * begin in its span, so neither a long string nor uneven ones leave lanes
+ * idle.  The others: wavefronts per string for sets above 16 words, and
  * for sets of 6-16 words when the strings number at most four per SIMD
  * (16 x compute units); otherwise one lane per string.  When the program's bit-sliced circuit is compiled
  * (rx_program_jit) and n >= 16384, a check on the device decides whether the
@@ -251,8 +255,9 @@ typedef struct {
  * it, the length of the shortest prefix in the language (k = len_i is a
  * whole-string match only when no shorter prefix matched).  Strings and
  * offsets as for rx_match; d_first is int64[n] on the device.  Runs the
- * table-form kernels (one lane per string up to 16 words, else one
- * wavefront per string), stopping each string at its first accept.  Errors
+ * table-form kernels (a searched program over spans as in rx_match, else one
+ * lane per string up to 16 words, else one wavefront per string), stopping
+ * each string at its first accept.  Errors
  * as rx_match. */
 int rx_match_first(const rx_program* prog, const uint8_t* d_bytes, const int64_t* d_offsets, int64_t n,
                    int64_t* d_first, void* stream);

@@ -51,6 +51,7 @@ int make_launch_args(const Program* P, const uint8_t* d_bytes, const int64_t* d_
     a->grid = 0;
     a->unroll = 0;
     a->stream = stream;
+    a->prefix = P->span_prefix;
     return RX_OK;
 }
 
@@ -176,6 +177,20 @@ int auto_table_variant(const Program* P, int64_t n) {
     if (hip_cu_count(&cus) || cus <= 0) cus = 256;
     return n <= 16 * (int64_t)cus ? RX_VARIANT_WAVE : RX_VARIANT_LANE;   // at most four wavefronts per SIMD
 }
+
+// The span kernels for a searched program, where the caller left the launch
+// shape open: a lane's work does not grow with the longest string.  Measured
+// against the form above (one lane or wavefront per string): 20,000 lines of
+// 1 to 4,096 bytes 20 against 600-700 us, 10^6 lines 236 against 1,890 us, 300
+// lines of 16 bytes on average 10 against 43 us; 200,000 records of 100 bytes
+// 40 against 48 us.  Few bytes in short records of one length are done sooner
+// with a lane each, in one launch instead of two: 50,000 of 10 bytes 11.5
+// against 14.8 us, of 21 bytes 16.2 against 15.8 us, 2 * 10^6 of 10 bytes 62
+// against 43 us.
+bool spans_ok(const Program* P, const LaunchArgs& a) {
+    if (P->span_prefix < 0 || a.block != 0 || a.grid != 0 || a.unroll != 0) return false;
+    return a.offsets || a.stride >= 20 || a.n >= ((int64_t)2 << 20) / (a.stride + 1);
+}
 }  // namespace
 
 int rx_match_ex(const rx_program* prog, const uint8_t* d_bytes, const int64_t* d_offsets, int64_t n,
@@ -195,6 +210,9 @@ int rx_match_ex(const rx_program* prog, const uint8_t* d_bytes, const int64_t* d
         a.grid = launch->grid;
         a.unroll = launch->unroll;
     }
+    const bool spans = variant == RX_VARIANT_AUTO && spans_ok(P, a);
+    if (spans)
+        if (int e = launch_spans_fill(a)) return hip_fail(e, "kernel launch (fill)");
     if (variant == RX_VARIANT_AUTO && n >= kLayoutMinStrings && jit_offsets_ready(P)) {
         // Equal-length consecutive strings go to the bit-sliced kernel: a
         // check on the device fills this call's layout slot, the sliced kernel
@@ -209,6 +227,10 @@ int rx_match_ex(const rx_program* prog, const uint8_t* d_bytes, const int64_t* d
             return hip_fail(e, "kernel launch (sliced)");
         a.skip = slot;
         a.skip_id = id;
+    }
+    if (spans) {
+        if (int e = launch_spans(a)) return hip_fail(e, "kernel launch (spans)");
+        return RX_OK;
     }
     if (variant == RX_VARIANT_AUTO) variant = auto_table_variant(P, n);
     int e;
@@ -463,7 +485,10 @@ int rx_match_first_fixed(const rx_program* prog, const uint8_t* d_bytes, int64_t
         a.stride = length;
         a.out = nullptr;
         a.first_pos = d_first;
-        if (P->W <= kLaneMaxWords) {
+        if (spans_ok(P, a)) {
+            e = launch_spans_fill(a);
+            if (!e) e = launch_spans(a);
+        } else if (P->W <= kLaneMaxWords) {
             e = launch_lane(a);
         } else {
             if (P->W > kWaveMaxWords) return fail(RX_ETOOBIG, "the wavefront kernel holds sets of at most 128 words");
@@ -489,7 +514,10 @@ int rx_match_first(const rx_program* prog, const uint8_t* d_bytes, const int64_t
     a.out = nullptr;
     a.first_pos = d_first;
     int e;
-    if (P->W <= kLaneMaxWords) {
+    if (spans_ok(P, a)) {
+        e = launch_spans_fill(a);
+        if (!e) e = launch_spans(a);
+    } else if (P->W <= kLaneMaxWords) {
         e = launch_lane(a);
     } else {
         if (P->W > kWaveMaxWords) return fail(RX_ETOOBIG, "the wavefront kernel holds sets of at most 128 words");
@@ -529,10 +557,15 @@ int rx_match_fixed_ex(const rx_program* prog, const uint8_t* d_bytes, int64_t le
     // A circuit of at most two words runs few or long strings chunk-parallel;
     // many short ones fill the chip better 32 strings to a lane.
     const bool chunks_ok = jit_chunks_ready(P) && length > 0;
+    const bool auto_chunks = chunks_ok && (length >= 32768 || n <= 4096);
+    if (variant == RX_VARIANT_AUTO && !auto_chunks && !sliced_ok && spans_ok(P, a)) {
+        int e = launch_spans_fill(a);
+        if (!e) e = launch_spans(a);
+        if (e) return hip_fail(e, "kernel launch (spans)");
+        return RX_OK;
+    }
     if (variant == RX_VARIANT_AUTO)
-        variant = chunks_ok && (length >= 32768 || n <= 4096) ? RX_VARIANT_CHUNKS
-                  : sliced_ok                                 ? RX_VARIANT_SLICED
-                                                              : auto_table_variant(P, n);
+        variant = auto_chunks ? RX_VARIANT_CHUNKS : sliced_ok ? RX_VARIANT_SLICED : auto_table_variant(P, n);
     int e;
     switch (variant) {
     case RX_VARIANT_CHUNKS:

@@ -110,6 +110,7 @@ int autotune_single(const Program* P, const uint8_t* d_bytes, const int64_t* d_o
         c.launch.grid = grid;
         cands.push_back(c);
     };
+    add(RX_VARIANT_AUTO, 0, 0);   // what rx_match picks by itself (a searched program's span kernel has no other name)
     const bool fixed = d_offsets == nullptr;
     if (fixed && jit_ready(P, nullptr, nullptr) && length > 0 && length % 16 == 0 &&
         (reinterpret_cast<uintptr_t>(d_bytes) & 15) == 0)

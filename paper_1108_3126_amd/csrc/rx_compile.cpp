@@ -314,6 +314,16 @@ int compile(const rx_ast_node* ast, int32_t n_ast, int32_t root, const rx_class*
         }
         P->suffix_any = sa;
     }
+    // A searched program that the span kernels take: the prefix leaf's image
+    // is First (a new match may begin after every byte), no other leaf leads
+    // back to it, and no match is empty.
+    if ((flags & RX_SEARCH) && P->suffix_any && !P->nullable && P->W <= kLaneMaxWords) {
+        const int32_t pre = P->leaf_rank[P->c0[P->c0[P->c0[0]]]];
+        bool ok = std::equal(P->first.begin(), P->first.end(), P->follow.begin() + (size_t)pre * W);
+        for (int32_t r = 0; r < L && ok; ++r)
+            ok = r == pre || !((P->follow[(size_t)r * W + (pre >> 5)] >> (pre & 31)) & 1u);
+        if (ok) P->span_prefix = pre;
+    }
 
     // device image
     auto align = [](int64_t x) { return (x + 255) & ~int64_t(255); };

@@ -39,6 +39,9 @@ struct Program {
     uint32_t flags = 0;
     int32_t L = 0, W = 0, height = 0;
     bool nullable = false, suffix_any = false;
+    // rank of the search prefix's any-byte leaf, for a searched program that
+    // runs over equal spans of bytes (rx_spans.h); -1: it does not
+    int32_t span_prefix = -1;
     std::vector<int32_t> leaf_node;  // rank -> node
     std::vector<int32_t> leaf_rank;  // node -> rank, -1 for internal nodes
     // evolution tables (Def. 5.1), 32-bit words
@@ -205,8 +208,14 @@ struct LaunchArgs {
     // bit-sliced kernel took the strings
     const int64_t* skip = nullptr;
     int64_t skip_id = 0;
+    int32_t prefix = -1;   // the program's span_prefix
 };
 int launch_lane(const LaunchArgs& a);
+// A searched program (span_prefix >= 0) over equal spans of bytes:
+// launch_spans_fill sets every result to "no match", launch_spans then sets
+// those of the strings that match.
+int launch_spans_fill(const LaunchArgs& a);
+int launch_spans(const LaunchArgs& a);
 // Equal-length consecutive strings for rx_match (rx_kernels.hip): the slot of
 // call `id` in a static per-device array of kLayoutSlots slots of four int64
 // {id, length, first offset, flaw}; launch_layout_check fills it on `stream`
