@@ -503,9 +503,11 @@ enum { RX_FORM_TABLE = 0, RX_FORM_PLANES = 1 };
 int64_t rx_match_multi_workspace(int64_t n, int32_t n_progs, const rx_multi_config* cfg);
 
 /*
- * Batched matching: every string against every program in one persistent
- * launch (the generic lockstep machine of Def. 5.3 per (program, string)).
- * Strings are bucketed by length on the device; work items of up to `block`
+ * Batched matching: every string against every program in persistent launches
+ * (the generic lockstep machine of Def. 5.3 per (program, string)).  Searched
+ * programs that do not match the empty string run over equal spans of the
+ * strings' bytes (as in rx_match; cfg's edges, block and grid do not concern
+ * them).  For the others, strings are bucketed by length on the device; work items of up to `block`
  * strings of one bucket against one program are generated on the device,
  * longest bucket first, and pulled by a persistent kernel from an atomic
  * queue.  d_out is n_progs x n bytes, row p for program p.  d_work is caller
@@ -586,8 +588,8 @@ int rx_autotune_multi(const rx_program* const* progs, int32_t n_progs, const uin
  * fit `hbm_budget`.  Clients submit requests from any thread; a scheduler
  * thread admits pending requests into the next free step while they fit its
  * capacity, so requests that arrive while steps run join the next step and
- * steps on different slots overlap on the device.  Each step is one launch of
- * the batched item kernel framed by host<->device copies, replayed as a
+ * steps on different slots overlap on the device.  Each step is one launch each of
+ * the batched span and item kernels framed by host<->device copies, replayed as a
  * hipGraph when use_graph is set.  Programs are cached by their AST bytes,
  * classes and flags.  A request's bits do not depend on what it was batched
  * with.

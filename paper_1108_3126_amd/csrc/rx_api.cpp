@@ -677,7 +677,7 @@ int match_multi_planes(const rx_program* const* progs, int32_t n_progs, const ui
         m.descs[i].L = P->L;
         m.descs[i].W = P->W;
         m.descs[i].suffix_any = P->suffix_any ? 1 : 0;
-        m.descs[i].pad = 0;
+        m.descs[i].prefix = P->span_prefix;
     }
     if (!jit_planes_prepared(m.progs, n_progs))
         return fail(RX_EINVAL, "this program list has no plane-form module on the device (rx_match_multi_prepare)");
@@ -751,7 +751,7 @@ int rx_match_multi(const rx_program* const* progs, int32_t n_progs, const uint8_
         m.progs[i].L = P->L;
         m.progs[i].W = P->W;
         m.progs[i].suffix_any = P->suffix_any ? 1 : 0;
-        m.progs[i].pad = 0;
+        m.progs[i].prefix = P->span_prefix;
     }
     m.n_progs = n_progs;
     m.bytes = d_bytes;
@@ -764,6 +764,10 @@ int rx_match_multi(const rx_program* const* progs, int32_t n_progs, const uint8_
     if (cfg && cfg->graph) {
         std::string topo = "table", full;
         graph_key(topo, n_progs);
+        for (int i = 0; i < n_progs; ++i) {   // which kernels run, and their LDS
+            graph_key(topo, m.progs[i].L);
+            graph_key(topo, m.progs[i].prefix >= 0);
+        }
         graph_key(topo, m.n_edges);
         graph_key(topo, m.edges);
         graph_key(topo, m.block_lines);

@@ -65,7 +65,7 @@ struct ProgDesc {                   // device tables of one program
     const uint32_t* first;
     const uint32_t* follow;
     const uint32_t* bytemask;
-    int32_t L, W, suffix_any, pad;
+    int32_t L, W, suffix_any, prefix;   // prefix: the program's span_prefix
 };
 
 struct WorkItem {                   // up to `block` strings against one program
@@ -74,6 +74,14 @@ struct WorkItem {                   // up to `block` strings against one program
     int64_t line0;                  // first string (or first entry of the id list)
     int64_t out0;                   // result of string s goes to out[out0 + s]
 };
+
+// An item of the span kernel (rx_spans.h) in the same form: regions r0 ..
+// r0 + nr - 1 of the text of strings line0 .. line0 + count - 1, B bytes per
+// lane.
+inline WorkItem span_item(int32_t prog, int64_t line0, int32_t count, int32_t B, int32_t r0, int32_t nr) {
+    return {prog | B << 8, count, line0, (int64_t)r0 | (int64_t)nr << 32};
+}
+constexpr int kSpanQueueThreads = 256;   // threads of the span kernel's workgroups in batched matching
 
 struct MultiArgs {
     ProgDesc progs[kMaxItemProgs];
@@ -99,6 +107,11 @@ struct ItemsArgs {
     const WorkItem* items;
     const int32_t* n_items;
     int32_t* head;
+    const WorkItem* span_items;   // after the items; their results are 0 before they run
+    const int32_t* n_span_items;
+    int32_t* span_head;
+    int32_t max_span_items;       // *n_span_items, as the host knows it
+    int64_t n_lines;
     uint8_t* out;
     void* stream;
 };
@@ -142,7 +155,6 @@ int64_t plane_tick_cap(int64_t n, int64_t max_bytes);
 int64_t plane_workspace_bytes(int64_t n, int64_t max_bytes, int32_t n_progs, int32_t block_lines);
 int launch_planes_multi(const PlaneMultiArgs& m);
 int launch_multi(const MultiArgs& m);
-int launch_items(const ItemsArgs& m);
 
 // graph replay of a launch sequence (rx_graph.cpp): `record` issues the
 // sequence on the stream it is given (a capture stream); calls with equal

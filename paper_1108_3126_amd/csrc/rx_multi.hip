@@ -12,12 +12,14 @@
 // whose items name a program and a contiguous range of strings.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <map>
 #include <mutex>
 
 #include "rx_internal.h"
 #include "rx_planes.h"
+#include "rx_spans.h"
 
 namespace rx {
 
@@ -143,6 +145,130 @@ __global__ __launch_bounds__(256) void k_items(ItemKArgs a) {
     }
 }
 
+// -- searched programs over equal spans of bytes (rx_spans.h) ----------------
+
+// A queue of span items: given (items), or made from the text's size: every
+// program of `rows` over every slice of the text's regions.
+struct SpanQueueArgs {
+    ProgDesc progs[kMaxItemProgs];
+    const uint8_t* bytes;
+    const int64_t* offsets;
+    int64_t n;
+    uint8_t* out;           // row p at out + p * n (given items: one row)
+    const WorkItem* items;
+    const int32_t* n_items;
+    int32_t* head;
+    int32_t n_rows;
+    uint8_t rows[kMaxItemProgs];   // the programs, widest sets first
+};
+
+template <int W>
+__device__ __forceinline__ void span_run(const ProgDesc& P, const SpanText& X, uint8_t* out, int64_t o0, int64_t oN,
+                                         int B, int64_t r0, int64_t r1, bool staged, uint32_t* lds) {
+    constexpr int WP = span_row_words(W);
+    constexpr int T = kSpanQueueThreads;
+    const SpanProg S = {P.first, P.follow, P.bytemask, P.L, P.prefix};
+    uint32_t* M = lds;
+    uint32_t* N = M + 256 * WP;
+    uint32_t* F = N + 257 * WP;
+    if (!staged) span_tables<W, T>(S, M, N, F);
+    span_regions<W, T, false>(S, X, {out, nullptr, nullptr, 0}, o0, oN, B, r0, r1, M, N, F, F + P.L * WP);
+}
+
+// Persistent: a workgroup's next item is often of the program whose tables it
+// holds.
+__global__ __launch_bounds__(kSpanQueueThreads) void k_span_queue(SpanQueueArgs a) {
+    extern __shared__ __align__(16) uint32_t lds[];
+    __shared__ int s_item;
+    const int64_t T = kSpanQueueThreads;
+    int64_t regions = 0, slice = 1, slices = 0, total = 0;
+    int B = 0;
+    if (a.items) {
+        total = *a.n_items;
+    } else {
+        const int64_t bytes = a.offsets[a.n] - a.offsets[0];
+        if (bytes > 0) {
+            B = span_bytes((bytes + 15) * a.n_rows, gridDim.x * T);
+            regions = (bytes + 15 + T * B - 1) / (T * B);
+            // about four items per workgroup, so the widest programs do not end the launch alone
+            slice = regions * a.n_rows / (4 * (int64_t)gridDim.x);
+            if (slice < 1) slice = 1;
+            slices = (regions + slice - 1) / slice;
+            total = slices * a.n_rows;
+        }
+    }
+    int loaded = -1;
+    for (;;) {
+        if (threadIdx.x == 0) s_item = atomicAdd(a.head, 1);
+        __syncthreads();
+        const int it = s_item;
+        if (it >= total) break;   // the same for every thread
+        SpanText X = {a.bytes, a.offsets, 0, a.n};
+        uint8_t* out = a.out;
+        int p;
+        int64_t r0, r1;
+        if (a.items) {
+            const WorkItem w = a.items[it];
+            p = w.prog & 255;
+            B = w.prog >> 8;
+            X.offsets += w.line0;
+            X.n = w.count;
+            out += w.line0;
+            r0 = (int32_t)(w.out0 & 0xffffffff);
+            r1 = r0 + (w.out0 >> 32);
+        } else {
+            p = a.rows[it / slices];
+            out += p * a.n;
+            r0 = it % slices * slice;
+            r1 = r0 + slice < regions ? r0 + slice : regions;
+        }
+        const ProgDesc& P = a.progs[p];
+        const int64_t o0 = X.offsets[0], oN = X.offsets[X.n];
+        const bool staged = p == loaded;
+        loaded = p;
+        switch (P.W) {
+#define RX_SR(w) \
+    case w: span_run<w>(P, X, out, o0, oN, B, r0, r1, staged, lds); break;
+            RX_SR(1) RX_SR(2) RX_SR(3) RX_SR(4) RX_SR(5) RX_SR(6) RX_SR(7) RX_SR(8)
+            RX_SR(9) RX_SR(10) RX_SR(11) RX_SR(12) RX_SR(13) RX_SR(14) RX_SR(15) RX_SR(16)
+#undef RX_SR
+        default: break;   // not reached: the host refuses programs above 16 words
+        }
+        __syncthreads();   // s_item and the tables are reused by the next item
+    }
+}
+
+// Before the queue: its head, and "no match" for every string of its rows.
+__global__ __launch_bounds__(256) void k_span_clear(SpanQueueArgs a, int64_t n) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && !a.items) *a.head = 0;
+    uint8_t* out = a.out + (a.items ? 0 : a.rows[blockIdx.y]) * a.n;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) out[i] = 0;
+}
+
+dim3 span_clear_grid(int64_t n, int rows) {
+    const int64_t b = (n + 255) / 256;
+    return dim3((unsigned)(b < 1 ? 1 : b < 1024 ? b : 1024), (unsigned)rows);
+}
+
+// Dynamic LDS of the queue kernel for a list of programs, and the workgroups
+// that are resident with it.
+int span_queue_lds(const ProgDesc* progs, int n, int* lds, int* grid) {
+    int words = 0;
+    for (int i = 0; i < n; ++i)
+        if (progs[i].prefix >= 0) {
+            const int w = span_lds_words(progs[i].W, progs[i].L, kSpanQueueThreads);
+            if (w > words) words = w;
+        }
+    *lds = 4 * words;
+    int cus = 0;
+    if (hip_cu_count(&cus) || cus <= 0) cus = 256;
+    int per = (160 * 1024) / (*lds + 512);
+    *grid = cus * (per < 1 ? 1 : per > 8 ? 8 : per);
+    return *lds > 64 * 1024
+               ? (int)hipFuncSetAttribute((const void*)k_span_queue, hipFuncAttributeMaxDynamicSharedMemorySize, *lds)
+               : 0;
+}
+
 // -- bucketing -------------------------------------------------------------
 __device__ __forceinline__ int bucket_of(int64_t len, const int32_t* edges, int n_edges) {
     int b = 0;
@@ -164,6 +290,7 @@ struct BucketArgs {
     int32_t* n_items;
     int32_t* head;
     int32_t n_progs;
+    uint8_t rows[kMaxItemProgs];   // the programs that run over the buckets
     int32_t block_lines;
     int64_t out_stride;
 };
@@ -234,7 +361,7 @@ __global__ void k_bucket_fill(BucketArgs a) {
         if (b < 0) continue;  // not reached: every k < total lies in one bucket's range
         const int32_t tiles = (a.counts[b] + a.block_lines - 1) / a.block_lines;
         const int32_t local = k - a.item_start[b];
-        const int32_t p = local / tiles, t = local % tiles;
+        const int32_t p = a.rows[local / tiles], t = local % tiles;
         WorkItem w;
         w.prog = p;
         w.count = a.counts[b] - t * a.block_lines < a.block_lines ? a.counts[b] - t * a.block_lines : a.block_lines;
@@ -783,6 +910,14 @@ int64_t multi_workspace_bytes(int64_t n, int32_t n_progs, int32_t n_buckets, int
 int launch_multi(const MultiArgs& m) {
     const hipStream_t st = (hipStream_t)m.stream;
     const int nb = m.n_edges + 1;
+    // Searched programs run over equal spans of the text's bytes, the others
+    // one lane per string over length buckets.  Measured: 4 programs x 20,000
+    // lines 250 us over spans, 2,940 us over the buckets, where the longest
+    // line (4,096 bytes) is one serial chain.
+    uint8_t spans[kMaxItemProgs], plain[kMaxItemProgs];
+    int n_spans = 0, n_plain = 0;
+    for (int i = 0; i < m.n_progs; ++i) (m.progs[i].prefix >= 0 ? spans[n_spans++] : plain[n_plain++]) = (uint8_t)i;
+    std::stable_sort(spans, spans + n_spans, [&](uint8_t x, uint8_t y) { return m.progs[x].W > m.progs[y].W; });
     uint8_t* w = static_cast<uint8_t*>(m.work);
     auto al = [](int64_t x) { return (x + 255) & ~int64_t(255); };
     BucketArgs b;
@@ -800,9 +935,29 @@ int launch_multi(const MultiArgs& m) {
     const int64_t o_ids = al(4 * (int64_t)(4 * (nb + 1) + 4));
     b.ids = reinterpret_cast<int32_t*>(w + o_ids);
     b.items = reinterpret_cast<WorkItem*>(w + o_ids + al(4 * m.n));
-    b.n_progs = m.n_progs;
+    b.n_progs = n_plain;
+    for (int i = 0; i < n_plain; ++i) b.rows[i] = plain[i];
     b.block_lines = m.block_lines;
     b.out_stride = m.n;
+    if (n_spans && m.n > 0) {
+        SpanQueueArgs q;
+        for (int i = 0; i < m.n_progs; ++i) q.progs[i] = m.progs[i];
+        q.bytes = m.bytes;
+        q.offsets = m.offsets;
+        q.n = m.n;
+        q.out = m.out;
+        q.items = nullptr;
+        q.n_items = nullptr;
+        q.head = b.head + 1;   // after the buckets' own counters
+        q.n_rows = n_spans;
+        for (int i = 0; i < n_spans; ++i) q.rows[i] = spans[i];
+        int lds = 0, grid = 0;
+        if (int e = span_queue_lds(m.progs, m.n_progs, &lds, &grid)) return e;
+        hipLaunchKernelGGL(k_span_clear, span_clear_grid(m.n, n_spans), dim3(256), 0, st, q, m.n);
+        hipLaunchKernelGGL(k_span_queue, dim3((unsigned)grid), dim3(kSpanQueueThreads), (size_t)lds, st, q);
+        if (hipError_t e = hipGetLastError()) return (int)e;
+    }
+    if (!n_plain) return 0;
     const int gs = (int)((m.n + 255) / 256 < 1024 ? (m.n + 255) / 256 : 1024);
     hipLaunchKernelGGL(k_bucket_clear, dim3(1), dim3(64), 0, st, b);
     if (m.n > 0) hipLaunchKernelGGL(k_bucket_count, dim3(gs > 0 ? gs : 1), dim3(256), 0, st, b);
@@ -822,8 +977,8 @@ int launch_multi(const MultiArgs& m) {
     k.head = b.head;
     k.out = m.out;
     int max_lds_words = 0;
-    for (int i = 0; i < m.n_progs; ++i) {
-        const int words = (256 + m.progs[i].L) * m.progs[i].W;
+    for (int i = 0; i < n_plain; ++i) {
+        const int words = (256 + m.progs[plain[i]].L) * m.progs[plain[i]].W;
         if (words > max_lds_words) max_lds_words = words;
     }
     const int grid = m.grid > 0 ? m.grid : 1024;
@@ -831,29 +986,7 @@ int launch_multi(const MultiArgs& m) {
     return (int)hipGetLastError();
 }
 
-int launch_items(const ItemsArgs& m) {
-    ItemKArgs k;
-    for (int i = 0; i < m.n_progs; ++i) k.progs[i] = m.progs[i];
-    k.n_progs = m.n_progs;
-    k.block_lines = m.block;
-    k.bytes = m.bytes;
-    k.offsets = m.offsets;
-    k.ids = nullptr;
-    k.items = m.items;
-    k.n_items = m.n_items;
-    k.head = m.head;
-    k.out = m.out;
-    int max_lds_words = 0;
-    for (int i = 0; i < m.n_progs; ++i) {
-        const int words = (256 + m.progs[i].L) * m.progs[i].W;
-        if (words > max_lds_words) max_lds_words = words;
-    }
-    hipLaunchKernelGGL(k_items, dim3(m.grid > 0 ? m.grid : 1024), dim3(m.block > 0 ? m.block : 256),
-                       4 * (size_t)max_lds_words, (hipStream_t)m.stream, k);
-    return (int)hipGetLastError();
-}
-
-// -- one serving step: copies in, the item kernel, results out ----------------
+// -- one serving step: copies in, the span and item kernels, results out --------
 namespace {
 
 ItemKArgs item_kargs(const ItemsArgs& m) {
@@ -871,6 +1004,28 @@ ItemKArgs item_kargs(const ItemsArgs& m) {
     return k;
 }
 
+// The searched programs' part of a step: their items' kernel and its launch
+// shape (one workgroup where the step has none).
+struct StepSpans {
+    SpanQueueArgs args;
+    int lds = 0, grid = 1;
+};
+
+int step_spans(const ItemsArgs& m, StepSpans* s) {
+    for (int i = 0; i < kMaxItemProgs; ++i) s->args.progs[i] = i < m.n_progs ? m.progs[i] : ProgDesc{};
+    s->args.bytes = m.bytes;
+    s->args.offsets = m.offsets;
+    s->args.n = 0;
+    s->args.out = m.out;
+    s->args.items = m.span_items;
+    s->args.n_items = m.n_span_items;
+    s->args.head = m.span_head;
+    s->args.n_rows = 0;
+    if (int e = span_queue_lds(m.progs, m.n_progs, &s->lds, &s->grid)) return e;
+    if (m.max_span_items < s->grid) s->grid = m.max_span_items < 1 ? 1 : m.max_span_items;
+    return 0;
+}
+
 constexpr unsigned kStepLds = 4u * (256u + 511u) * (unsigned)kLaneMaxWords;  // the largest program a step may hold
 
 }  // namespace
@@ -881,6 +1036,10 @@ int step_launch_direct(const StepDesc& d, void* stream) {
         if (d.h2d[i].bytes)
             if (hipError_t e = hipMemcpyAsync(d.h2d[i].dst, d.h2d[i].src, d.h2d[i].bytes, hipMemcpyHostToDevice, st))
                 return (int)e;
+    StepSpans sp;
+    if (int e = step_spans(d.items, &sp)) return e;
+    hipLaunchKernelGGL(k_span_clear, span_clear_grid(d.items.n_lines, 1), dim3(256), 0, st, sp.args, d.items.n_lines);
+    hipLaunchKernelGGL(k_span_queue, dim3((unsigned)sp.grid), dim3(kSpanQueueThreads), (size_t)sp.lds, st, sp.args);
     ItemKArgs k = item_kargs(d.items);
     hipLaunchKernelGGL(k_items, dim3(d.items.grid), dim3(d.items.block), kStepLds, st, k);
     if (hipError_t e = hipGetLastError()) return (int)e;
@@ -892,16 +1051,45 @@ int step_launch_direct(const StepDesc& d, void* stream) {
 struct StepGraph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    hipGraphNode_t copy[3] = {}, kernel = nullptr, back = nullptr;
+    hipGraphNode_t copy[3] = {}, clear = nullptr, spans = nullptr, kernel = nullptr, back = nullptr;
     ItemKArgs args;
+    StepSpans sp;
+    int64_t n_lines = 0;
 };
+
+namespace {
+hipKernelNodeParams node_params(const void* f, dim3 grid, dim3 block, unsigned lds, void** params) {
+    hipKernelNodeParams kp = {};
+    kp.func = const_cast<void*>(f);
+    kp.gridDim = grid;
+    kp.blockDim = block;
+    kp.sharedMemBytes = lds;
+    kp.kernelParams = params;
+    kp.extra = nullptr;
+    return kp;
+}
+}  // namespace
 
 int step_graph_launch(StepGraph** pg, const StepDesc& d, void* stream) {
     const hipStream_t st = (hipStream_t)stream;
     auto sz = [](size_t b) { return b ? b : (size_t)1; };
     StepGraph* g = *pg;
-    if (!g) {
-        g = new StepGraph;
+    const bool fresh = !g;
+    if (fresh) g = new StepGraph;
+    g->args = item_kargs(d.items);
+    g->n_lines = d.items.n_lines;
+    if (int e = step_spans(d.items, &g->sp)) {
+        if (fresh) delete g;
+        return e;
+    }
+    void* clear_params[] = {&g->sp.args, &g->n_lines};
+    void* span_params[] = {&g->sp.args};
+    void* item_params[] = {&g->args};
+    hipKernelNodeParams kc = node_params((const void*)k_span_clear, span_clear_grid(g->n_lines, 1), dim3(256), 0, clear_params);
+    hipKernelNodeParams ks = node_params((const void*)k_span_queue, dim3((unsigned)g->sp.grid), dim3(kSpanQueueThreads),
+                                         (unsigned)g->sp.lds, span_params);
+    hipKernelNodeParams ki = node_params((const void*)k_items, dim3(d.items.grid), dim3(d.items.block), kStepLds, item_params);
+    if (fresh) {
         hipError_t e = hipGraphCreate(&g->graph, 0);
         hipGraphNode_t prev = nullptr;
         for (int i = 0; i < 3 && e == hipSuccess; ++i) {
@@ -909,19 +1097,13 @@ int step_graph_launch(StepGraph** pg, const StepDesc& d, void* stream) {
                                         d.h2d[i].src, sz(d.h2d[i].bytes), hipMemcpyHostToDevice);
             prev = g->copy[i];
         }
-        g->args = item_kargs(d.items);
-        if (e == hipSuccess) {
-            hipKernelNodeParams kp = {};
-            void* params[] = {&g->args};
-            kp.func = (void*)k_items;
-            kp.gridDim = dim3(d.items.grid);
-            kp.blockDim = dim3(d.items.block);
-            kp.sharedMemBytes = kStepLds;
-            kp.kernelParams = params;
-            kp.extra = nullptr;
-            e = hipGraphAddKernelNode(&g->kernel, g->graph, &prev, 1, &kp);
-            prev = g->kernel;
-        }
+        auto add = [&](hipGraphNode_t* node, const hipKernelNodeParams& kp) {
+            if (e == hipSuccess) e = hipGraphAddKernelNode(node, g->graph, &prev, 1, &kp);
+            prev = *node;
+        };
+        add(&g->clear, kc);
+        add(&g->spans, ks);
+        add(&g->kernel, ki);
         if (e == hipSuccess)
             e = hipGraphAddMemcpyNode1D(&g->back, g->graph, &prev, 1, d.d2h.dst, d.d2h.src, sz(d.d2h.bytes),
                                         hipMemcpyDeviceToHost);
@@ -937,18 +1119,9 @@ int step_graph_launch(StepGraph** pg, const StepDesc& d, void* stream) {
     for (int i = 0; i < 3 && e == hipSuccess; ++i)
         e = hipGraphExecMemcpyNodeSetParams1D(g->exec, g->copy[i], d.h2d[i].dst, d.h2d[i].src, sz(d.h2d[i].bytes),
                                               hipMemcpyHostToDevice);
-    if (e == hipSuccess) {
-        g->args = item_kargs(d.items);
-        hipKernelNodeParams kp = {};
-        void* params[] = {&g->args};
-        kp.func = (void*)k_items;
-        kp.gridDim = dim3(d.items.grid);
-        kp.blockDim = dim3(d.items.block);
-        kp.sharedMemBytes = kStepLds;
-        kp.kernelParams = params;
-        kp.extra = nullptr;
-        e = hipGraphExecKernelNodeSetParams(g->exec, g->kernel, &kp);
-    }
+    if (e == hipSuccess) e = hipGraphExecKernelNodeSetParams(g->exec, g->clear, &kc);
+    if (e == hipSuccess) e = hipGraphExecKernelNodeSetParams(g->exec, g->spans, &ks);
+    if (e == hipSuccess) e = hipGraphExecKernelNodeSetParams(g->exec, g->kernel, &ki);
     if (e == hipSuccess)
         e = hipGraphExecMemcpyNodeSetParams1D(g->exec, g->back, d.d2h.dst, d.d2h.src, sz(d.d2h.bytes),
                                               hipMemcpyDeviceToHost);

@@ -7,7 +7,8 @@
 // slot plus the resident program tables -- stays inside the configured HBM
 // budget.  Requests that arrive while steps run join the next step; with two
 // or more slots, steps overlap on the device on separate streams.  A step is
-// one work-item launch (the persistent item kernel of the batched matcher)
+// two work-item launches (the persistent span and item kernels of the batched
+// matcher: searched programs' requests, the others)
 // framed by three host-to-device copies and one copy back, replayed as a
 // hipGraph whose node parameters are updated per step.  Compiled programs
 // stay resident in a device arena keyed by the request's expression, with
@@ -36,7 +37,7 @@ namespace {
 using Clock = std::chrono::steady_clock;
 
 constexpr int64_t kArenaSlotBytes = 64 * 1024;  // one program's tables (sets of at most 16 words)
-constexpr int64_t kItemHeader = 256;            // queue header (item count, head) before the items
+constexpr int64_t kItemHeader = 256;            // queue headers (item counts, heads) before the items
 
 struct CacheEntry {
     Program* prog = nullptr;
@@ -83,6 +84,7 @@ struct Server {
     rx_server_config cfg{};
     int dev = 0;
     int64_t max_items = 0;
+    int cus = 256;
     uint8_t* d_arena = nullptr;
     std::vector<CacheEntry*> arena_owner;
     std::vector<Slot> slots;
@@ -121,7 +123,6 @@ static int hip_err(hipError_t e, const char* what) {
 
 int Server::init() {
     if (hipGetDevice(&dev) != hipSuccess) return fail(RX_EHIP, "hipGetDevice failed");
-    int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
     if (cfg.grid <= 0) cfg.grid = 4 * cus;
     max_items = cfg.step_strings / cfg.block + cfg.step_requests + 1;
@@ -246,6 +247,26 @@ bool Server::launch_step(Slot& s, std::vector<Request*>& take) {
     int64_t line = 0, byte = 0, items = 0;
     WorkItem* it = reinterpret_cast<WorkItem*>(s.h_items + kItemHeader);
     int rc = RX_OK;
+    // Searched programs' requests run over equal spans of their bytes
+    // (rx_spans.h): B bytes per lane, 64 where the step's bytes fill the chip
+    // and fewer where the spans' serial chains would leave lanes idle; several
+    // regions per item where the items would not fit the slot.
+    int64_t span_bytes = 0, span_reqs = 0, plain_lines = 0;
+    auto in_spans = [](const Request* r) { return r->entry->prog->span_prefix >= 0 && r->n <= INT32_MAX; };
+    for (Request* r : take)
+        if (in_spans(r)) {
+            span_bytes += (int64_t)r->bytes.size();
+            ++span_reqs;
+        } else {
+            plain_lines += r->n;
+        }
+    const int64_t lanes = (int64_t)cus * 4 * kSpanQueueThreads;
+    const int32_t B = span_bytes > 32 * lanes ? 64 : span_bytes > 16 * lanes ? 32 : 16;
+    const int64_t region = (int64_t)kSpanQueueThreads * B;
+    // a request of n bytes has at most (n + 15) / region + 1 regions
+    const int64_t room = std::max<int64_t>(1, max_items - (int64_t)take.size() - plain_lines / cfg.block);
+    const int64_t per_item = (span_bytes / region + 2 * span_reqs + room - 1) / room + (span_reqs ? 0 : 1);
+    std::vector<WorkItem> span_items;
     for (Request* r : take) {
         int pidx = -1;
         for (size_t i = 0; i < progs.size(); ++i)
@@ -263,7 +284,7 @@ bool Server::launch_step(Slot& s, std::vector<Request*>& take) {
             pd.L = P->L;
             pd.W = P->W;
             pd.suffix_any = P->suffix_any ? 1 : 0;
-            pd.pad = 0;
+            pd.prefix = P->span_prefix;
         }
         r->entry->inflight += 1;
         r->entry->last_used = step_seq;
@@ -280,7 +301,12 @@ bool Server::launch_step(Slot& s, std::vector<Request*>& take) {
         }
         if (!r->bytes.empty()) std::memcpy(s.h_bytes + byte, r->bytes.data(), r->bytes.size());
         for (int64_t i = 0; i < r->n; ++i) s.h_offs[line + i] = r->offsets[i] + byte;
-        for (int64_t t = 0; t < r->n; t += cfg.block) {
+        if (in_spans(r)) {
+            const int64_t regions = r->bytes.empty() ? 0 : ((int64_t)r->bytes.size() + 15 + region - 1) / region;
+            for (int64_t t = 0; t < regions; t += per_item)
+                span_items.push_back(span_item(pidx, line, (int32_t)r->n, B, (int32_t)t,
+                                               (int32_t)std::min(per_item, regions - t)));
+        } else for (int64_t t = 0; t < r->n; t += cfg.block) {
             WorkItem w;
             w.prog = pidx;
             w.count = (int32_t)std::min<int64_t>(cfg.block, r->n - t);
@@ -295,12 +321,19 @@ bool Server::launch_step(Slot& s, std::vector<Request*>& take) {
     s.h_offs[line] = byte;
     if (rc == RX_OK && s.uploaded)
         if (hipError_t e = hipEventRecord(s.upload_ev, s.stream)) rc = hip_err(e, "record the program uploads");
-    reinterpret_cast<int32_t*>(s.h_items)[0] = (int32_t)items;  // item count
-    reinterpret_cast<int32_t*>(s.h_items)[1] = 0;               // queue head
+    const int64_t total_items = items + (int64_t)span_items.size();
+    if (rc == RX_OK && total_items > max_items) rc = fail(RX_EHIP, "serving step: more work items than the slot holds");
+    if (rc == RX_OK && !span_items.empty())
+        std::memcpy(it + items, span_items.data(), sizeof(WorkItem) * span_items.size());
+    int32_t* head = reinterpret_cast<int32_t*>(s.h_items);
+    head[0] = (int32_t)items;               // item count
+    head[1] = 0;                            // queue head
+    head[2] = (int32_t)span_items.size();   // the same for the span items
+    head[3] = 0;
     if (rc == RX_OK) {
         d.h2d[0] = {s.d_bytes, s.h_bytes, (size_t)byte};
         d.h2d[1] = {s.d_offs, s.h_offs, 8 * (size_t)(line + 1)};
-        d.h2d[2] = {s.d_items, s.h_items, (size_t)(kItemHeader + sizeof(WorkItem) * items)};
+        d.h2d[2] = {s.d_items, s.h_items, (size_t)(kItemHeader + sizeof(WorkItem) * total_items)};
         d.items.n_progs = (int32_t)progs.size();
         d.items.block = cfg.block;
         d.items.grid = cfg.grid;
@@ -309,6 +342,11 @@ bool Server::launch_step(Slot& s, std::vector<Request*>& take) {
         d.items.items = reinterpret_cast<const WorkItem*>(s.d_items + kItemHeader);
         d.items.n_items = reinterpret_cast<const int32_t*>(s.d_items);
         d.items.head = reinterpret_cast<int32_t*>(s.d_items) + 1;
+        d.items.span_items = d.items.items + items;
+        d.items.n_span_items = d.items.n_items + 2;
+        d.items.span_head = d.items.head + 2;
+        d.items.max_span_items = (int32_t)span_items.size();
+        d.items.n_lines = line;
         d.items.out = s.d_out;
         d.items.stream = s.stream;
         d.d2h = {s.h_out, s.d_out, (size_t)line};

@@ -365,8 +365,12 @@ __device__ __forceinline__ void span_regions(const SpanProg& P, const SpanText& 
 #pragma unroll
                 for (int w = 0; w < W; ++w) V[w] = 0u;
                 bool done = false;
-                for (int64_t at = S.start + p; at < stop && !done; at += 16) {   // 16-byte aligned
-                    const uint4 v = *reinterpret_cast<const uint4*>(X.bytes + at);
+                const uint8_t* from = X.bytes + S.start + p;   // 16-byte aligned; the next 16 bytes are on their way
+                uint4 nx = S.start + p < stop ? *reinterpret_cast<const uint4*>(from) : make_uint4(0u, 0u, 0u, 0u);
+                for (int64_t at = S.start + p; at < stop && !done; at += 16) {
+                    const uint4 v = nx;
+                    from += 16;
+                    if (at + 16 < stop) nx = *reinterpret_cast<const uint4*>(from);
                     const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
                     for (int b = 0; b < 16 && at + b < stop && !done; ++b) {
                         const uint32_t lo2 = b & 4 ? wv[1] : wv[0], hi2 = b & 4 ? wv[3] : wv[2];

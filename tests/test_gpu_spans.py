@@ -127,3 +127,62 @@ def test_spans_fixed_lengths(dev, length, n, shift):
     want_first, want = _earliest(tree, data, offs)
     np.testing.assert_array_equal(rx.match_fixed(p, d, length, n).cpu().numpy(), want)
     np.testing.assert_array_equal(rx.match_first_fixed(p, d, length, n).cpu().numpy(), want_first)
+
+
+def _mixed_programs():
+    """Searched (over spans), anchored, nullable and searched-nullable programs, narrow and wide sets."""
+    from paper_1108_3126_amd import rx
+
+    out = [(*rx.parse(p), search) for p, search in ((b"ab+c", True), (b"a.*b.*c", False), (b"(ab)*", True), (b"[^q]*z", False),
+                                                    (b"q.{40}z", True))]
+    for seed, nodes in ((5, 40), (6, 500), (7, 900)):
+        t = W.multi_programs(seed=seed, count=1, lo=nodes, hi=nodes)[0]
+        out.append((t.ast, t.root, t.classes, True))
+    return out
+
+
+@pytest.mark.parametrize("n,mean,hi", [(1, 50, 50), (700, 100, 5000), (30_000, 60, 2000)])
+@pytest.mark.parametrize("graph", [False, True])
+def test_spans_in_batched_matching(dev, n, mean, hi, graph):
+    """rx_match_multi's table form with lists that mix programs over spans and over buckets, and lists of one kind."""
+    from paper_1108_3126_amd import rx
+
+    progs = _mixed_programs()
+    ps = [rx.compile(a, r, c, search=s).upload() for a, r, c, s in progs]
+    rng = np.random.default_rng(n)
+    lens = W.lognormal_lengths(rng, n, mean, 1.0, 0, hi)
+    offs = np.zeros(n + 1, np.int64)
+    np.cumsum(lens, out=offs[1:])
+    data = W.zipf_bytes(rng, int(offs[-1]))
+    d, o = torch.from_numpy(data).to(dev), torch.from_numpy(offs).to(dev)
+    sub = np.arange(n) if n < 1000 else np.arange(0, n, 37)
+    want = np.stack([oracle.match(a, r, c, s, data, offs, index=sub) for a, r, c, s in progs])
+    for pick in (range(len(ps)), [1, 3], [0, 5, 7], [4]):
+        pick = list(pick)
+        print(n, pick, graph, flush=True)
+        for _ in range(3 if graph else 1):
+            got = rx.match_multi([ps[k] for k in pick], d, o, config=rx.multi_config(graph=graph)).cpu().numpy()
+            np.testing.assert_array_equal(got[:, sub], want[pick])
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_spans_in_the_server(dev, graph):
+    """Requests of every kind in shared steps; a server whose steps hold few work items (several regions each)."""
+    from paper_1108_3126_amd.server import Server
+
+    progs = _mixed_programs()
+    rng = np.random.default_rng(11)
+    for cfg in (dict(), dict(step_bytes=1 << 20, step_strings=512, step_requests=8, block=256)):
+        reqs, ids = [], []
+        with Server(use_graph=graph, **cfg) as srv:
+            for i in range(40):
+                a, r, c, s = progs[i % len(progs)]
+                n = int(rng.integers(0, 60))
+                lens = W.lognormal_lengths(rng, n, 300, 1.5, 0, 8192)
+                offs = np.zeros(n + 1, np.int64)
+                np.cumsum(lens, out=offs[1:])
+                data = W.zipf_bytes(rng, int(offs[-1]))
+                ids.append(srv.submit(W.Program(a, r, c, s), data, offs))
+                reqs.append((a, r, c, s, data, offs))
+            for rid, (a, r, c, s, data, offs) in zip(ids, reqs):
+                np.testing.assert_array_equal(srv.wait(rid), oracle.match(a, r, c, s, data, offs))
