@@ -358,21 +358,28 @@ std::string jit_step_source(const Program& P, int* n_state, int* n_ops, int* suf
             number();
             continue;
         }
-        // commit the new state after every value is computed
-        std::ostringstream tail;
+        // Commit the new state after every value is computed.  An update that
+        // is another word as it was (a leaf that any byte moves on) is read
+        // before any word changes.
+        std::ostringstream olds, tail;
+        auto value = [&](const V& v, const std::string& name) {
+            if (v.c >= 0 || v.n.rfind("s[", 0) != 0) return Emitter::str(v);
+            olds << "    const u32 " << name << " = " << v.n << ";\n";
+            return name;
+        };
         std::vector<char> done(ns > 0 ? ns : 1, 0);
         for (int r = 0; r < P.L; ++r) {
             const int x = P.leaf_node[r];
             if (slot[x] < 0 || done[slot[x]]) continue;
             done[slot[x]] = 1;
-            tail << "    s[" << slot[x] << "] = " << Emitter::str(in[x]) << ";\n";
+            tail << "    s[" << slot[x] << "] = " << value(in[x], "o" + std::to_string(slot[x])) << ";\n";
         }
-        tail << "    acc = " << Emitter::str(out[0]) << ";\n";
+        tail << "    acc = " << value(out[0], "oacc") << ";\n";
         std::ostringstream src;
         src << "#define RX_NS " << (ns > 0 ? ns : 1) << "\n";
         src << "__device__ __forceinline__ void rx_step(u32 (&s)[RX_NS], u32& acc, u32 b0, u32 b1, u32 b2, u32 b3,"
                " u32 b4, u32 b5, u32 b6, u32 b7) {\n";
-        src << E.code.str() << tail.str() << "}\n";
+        src << E.code.str() << olds.str() << tail.str() << "}\n";
         src << "__device__ __forceinline__ void rx_init(u32 (&s)[RX_NS], u32& acc) {\n";
         for (int k = 0; k < (ns > 0 ? ns : 1); ++k) src << "    s[" << k << "] = 0u;\n";
         std::fill(done.begin(), done.end(), 0);
