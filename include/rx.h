@@ -197,10 +197,12 @@ int rx_program_upload(rx_program* prog, void* d_buf, size_t cap, void* stream);
  * string, with a set of at most 16 words, runs over equal spans of the strings' bytes, one
  * lane per span of 16, 32 or 64 bytes: every lane follows the matches that
  * begin in its span, so neither a long string nor uneven ones leave lanes
- * idle.  The others: wavefronts per string for sets above 16 words, and
+ * idle.  With a compiled circuit of at most 64 words (rx_program_jit) and
+ * enough strings, the circuit runs over spans of 16 bytes instead, 2,048 of
+ * them to a wavefront.  The others: wavefronts per string for sets above 16 words, and
  * for sets of 6-16 words when the strings number at most four per SIMD
  * (16 x compute units); otherwise one lane per string.  When the program's bit-sliced circuit is compiled
- * (rx_program_jit) and n >= 16384, a check on the device decides whether the
+ * (rx_program_jit) and n >= 16384 (524288 where the circuit runs over spans), a check on the device decides whether the
  * strings are equal-length and consecutive (offsets[i] = offsets[0] + i * len,
  * len a multiple of 16 up to 2^26, d_bytes + offsets[0] 16-byte aligned); if
  * so the bit-sliced kernel of rx_match_fixed matches them and the table-form
@@ -266,7 +268,7 @@ int rx_match_first(const rx_program* prog, const uint8_t* d_bytes, const int64_t
  * (i+1)*length)).  With a compiled circuit (rx_program_jit), 16-byte aligned
  * bytes and length % 16 == 0 (length <= 2^26), the skewed bit-sliced kernel
  * runs, recording each string's first accept as it appears; otherwise the
- * table-form kernels.  d_first: caller-owned device int64[n]; entry i = the
+ * table-form kernels; over spans where rx_match_fixed would.  d_first: caller-owned device int64[n]; entry i = the
  * length of the shortest prefix of string i that the program accepts (with
  * RX_SEARCH: where the earliest-ending match ends), -1 if none.  A program
  * whose root is nullable answers 0 for every string without matching.
@@ -303,7 +305,13 @@ int rx_match_first_fixed(const rx_program* prog, const uint8_t* d_bytes, int64_t
  * state; the workspace holds every chunk's map (4 (words + 1) bytes per chunk,
  * chunks of at least 16 bytes, at most about 2,048 x 2,048 of them) and the
  * segments' maps.
- * rx_match_long_workspace(.., chunks = 0, ..) covers both forms.
+ * With chunks = 0, a searched program that does not match the empty string (a set of
+ * at most 16 words) and a string of 4,096 bytes or more, spans of the string
+ * run first, as in rx_match; only if a thread outlives its span by more than
+ * 4,096 bytes (or the circuit's region), which the device finds, do the kernels
+ * above run too (they are queued either way, and return at once; the
+ * device's finding is kept in a slot as for rx_match).
+ * rx_match_long_workspace(.., chunks = 0, ..) covers all forms.
  * Errors: RX_EINVAL (NULL buffers, negative sizes, short workspace),
  * RX_ENOTUPLOADED, RX_ETOOBIG (sets above 128 words), RX_EHIP. */
 int rx_match_long_workspace(const rx_program* prog, int64_t length, int32_t chunks, size_t* bytes);
@@ -371,7 +379,10 @@ int rx_match_ex(const rx_program* prog, const uint8_t* d_bytes, const int64_t* d
  * No offsets array is read.  With a run-time compiled bit-sliced circuit
  * (rx_program_jit), a 16-byte aligned d_bytes and length a multiple of 16,
  * the sliced kernel runs (one lane advances 32 strings per instruction);
- * otherwise the table-form kernels run.  Same results either way.
+ * otherwise the table-form kernels run.  A searched program's strings run over
+ * spans, as in rx_match, where that is faster: lengths and addresses that the
+ * sliced kernel does not take, and fewer than 524288 strings of 64 bytes or
+ * more.  Same results either way.
  * Errors: RX_EINVAL, RX_ENOTUPLOADED, RX_EHIP.
  */
 int rx_match_fixed(const rx_program* prog, const uint8_t* d_bytes, int64_t length, int64_t n, uint8_t* d_out,

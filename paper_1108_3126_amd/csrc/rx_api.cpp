@@ -178,6 +178,12 @@ int auto_table_variant(const Program* P, int64_t n) {
     return n <= 16 * (int64_t)cus ? RX_VARIANT_WAVE : RX_VARIANT_LANE;   // at most four wavefronts per SIMD
 }
 
+// Identities of the calls that use a layout slot (see layout_slot).
+int64_t next_slot_id() {
+    static std::atomic<int64_t> next_id{0};
+    return ++next_id;
+}
+
 // The span kernels for a searched program, where the caller left the launch
 // shape open: a lane's work does not grow with the longest string.  Measured
 // against the form above (one lane or wavefront per string): 20,000 lines of
@@ -190,6 +196,38 @@ int auto_table_variant(const Program* P, int64_t n) {
 bool spans_ok(const Program* P, const LaunchArgs& a) {
     if (P->span_prefix < 0 || a.block != 0 || a.grid != 0 || a.unroll != 0) return false;
     return a.offsets || a.stride >= 20 || a.n >= ((int64_t)2 << 20) / (a.stride + 1);
+}
+// Spans over the compiled circuit or over the tables.  A circuit's wavefront
+// works through 32 KB whatever the text's size, so it begins at about 25 us;
+// the tables begin at 13 us and take longer per byte, the more the wider the
+// sets.  Measured, lines of 120 bytes on average: one word, 100,000 lines 29
+// (circuit) and 20 us (tables), 200,000 31 and 29, 10^6 79 and 106; three
+// words, 50,000 lines 33 and 25, 100,000 36 and 38, 10^6 109 and 230; five
+// words, 50,000 lines 28 and 33.  With offsets the bytes are not known on the
+// host, so the strings' number stands for them.
+bool circuit_spans(const Program* P, const LaunchArgs& a) {
+    if (!jit_spans_ready(P)) return false;
+    const bool narrow = P->W <= 2;
+    if (a.offsets) return a.n >= (narrow ? 200000 : 65536);
+    return (double)a.n * (double)a.stride >= (narrow ? 24e6 : 8e6);
+}
+
+// Fixed-length strings that the bit-sliced kernels take too.  A wavefront of
+// theirs holds 2,048 strings whatever their number, and the chip 512 such
+// sets: fewer strings take as long as a full chip's.  Spans take the time of
+// the bytes.  Measured, a 17-word circuit, strings of 256 bytes: 20,000 18
+// (spans) and 72 us (sliced), 250,000 41 and 73, 500,000 71 and 77, 600,000 84
+// and 85; of 64 bytes: 250,000 21 and 28, 600,000 39 and 31; of 16 bytes: 19
+// and 18, 20 and 18.
+constexpr int64_t kSlicedStrings = 512 * 1024;
+bool spans_over_sliced(const Program* P, const LaunchArgs& a) {
+    if (!spans_ok(P, a) || a.stride < 64 || a.n >= kSlicedStrings) return false;
+    return jit_spans_ready(P) || (double)a.n * (double)a.stride < 8e6;
+}
+
+// No match everywhere, then the strings that match.
+int run_spans(const Program* P, const LaunchArgs& a) {
+    return circuit_spans(P, a) ? launch_span_circuit(P, a) : launch_spans(a);
 }
 }  // namespace
 
@@ -213,13 +251,15 @@ int rx_match_ex(const rx_program* prog, const uint8_t* d_bytes, const int64_t* d
     const bool spans = variant == RX_VARIANT_AUTO && spans_ok(P, a);
     if (spans)
         if (int e = launch_spans_fill(a)) return hip_fail(e, "kernel launch (fill)");
-    if (variant == RX_VARIANT_AUTO && n >= kLayoutMinStrings && jit_offsets_ready(P)) {
+    // (over spans, equal lengths are worth the check only from where the
+    // bit-sliced kernel is the faster one)
+    const int64_t check_from = spans && jit_spans_ready(P) ? kSlicedStrings : kLayoutMinStrings;
+    if (variant == RX_VARIANT_AUTO && n >= check_from && jit_offsets_ready(P)) {
         // Equal-length consecutive strings go to the bit-sliced kernel: a
         // check on the device fills this call's layout slot, the sliced kernel
         // runs if the slot says so, and the table-form launch below does
         // nothing in that case (and everything otherwise).
-        static std::atomic<int64_t> next_id{0};
-        const int64_t id = ++next_id;
+        const int64_t id = next_slot_id();
         int64_t* slot = nullptr;
         if (int e = layout_slot(id, &slot)) return hip_fail(e, "layout slot");
         if (int e = launch_layout_check(d_offsets, n, d_bytes, slot, id, stream)) return hip_fail(e, "layout check");
@@ -229,7 +269,7 @@ int rx_match_ex(const rx_program* prog, const uint8_t* d_bytes, const int64_t* d
         a.skip_id = id;
     }
     if (spans) {
-        if (int e = launch_spans(a)) return hip_fail(e, "kernel launch (spans)");
+        if (int e = run_spans(P, a)) return hip_fail(e, "kernel launch (spans)");
         return RX_OK;
     }
     if (variant == RX_VARIANT_AUTO) variant = auto_table_variant(P, n);
@@ -304,8 +344,9 @@ namespace {
 // The two launches of a chunk-parallel run over C chunks of cl bytes, with the
 // rows in d_work (long_rows_bytes(P, C) bytes; every row is written before it
 // is read, so the workspace needs no clearing).
+// (gate: see LongGate)
 int match_long_run(const Program* P, const uint8_t* d_bytes, int64_t length, int64_t C, int64_t cl, void* d_work,
-                   uint8_t* d_out, void* stream) {
+                   uint8_t* d_out, const LongGate& gate, void* stream) {
     LaunchArgs a;
     const int64_t rows = long_rows(P, C);
     if (int rc = make_launch_args(P, d_bytes ? d_bytes : static_cast<const uint8_t*>(d_work),
@@ -317,10 +358,36 @@ int match_long_run(const Program* P, const uint8_t* d_bytes, int64_t length, int
     a.rows_len = length;
     a.rows_cl = cl;
     a.rows_per_chunk = P->L + 1;
+    a.skip = gate.slot;
+    a.skip_id = gate.id;
     int e = P->W <= kLaneMaxWords ? launch_lane(a) : launch_wave(a);
     if (e) return hip_fail(e, "kernel launch (rows)");
-    e = launch_compose(a.rows_out, C, P->L + 1, P->W, P->L, P->suffix_any ? 1 : 0, d_out, stream);
+    e = launch_compose(a.rows_out, C, P->L + 1, P->W, P->L, P->suffix_any ? 1 : 0, d_out, gate, stream);
     if (e) return hip_fail(e, "kernel launch (composition)");
+    return RX_OK;
+}
+
+// One long string over spans, with a layout slot for what is undone; gate->slot
+// stays NULL where that does not apply (no such program, a short string, a chunk
+// count that the caller chose).  Measured, a 17-word circuit, text without a
+// match: 8 MiB 19 us (147 us as circuit chunks, each run from every word
+// alone).
+int long_spans(const Program* P, const uint8_t* d_bytes, int64_t length, int32_t chunks, uint8_t* d_out,
+               int64_t* d_first, LongGate* gate, void* stream) {
+    if (P->span_prefix < 0 || chunks != 0 || length < 4096) return RX_OK;
+    gate->id = next_slot_id();
+    int64_t* slot = nullptr;
+    if (int e = layout_slot(gate->id, &slot)) return hip_fail(e, "layout slot");
+    gate->slot = slot;
+    if (int e = launch_span_long_begin(*gate, d_out, d_first, stream)) return hip_fail(e, "kernel launch (spans)");
+    LaunchArgs a;
+    if (int rc = make_launch_args(P, d_bytes, slot, 1, reinterpret_cast<uint8_t*>(slot), stream, &a)) return rc;
+    a.offsets = nullptr;
+    a.stride = length;
+    a.out = d_out;
+    a.first_pos = d_first;
+    a.undone = slot + 3;
+    if (int e = run_spans(P, a)) return hip_fail(e, "kernel launch (spans)");
     return RX_OK;
 }
 
@@ -344,8 +411,10 @@ int rx_match_long(const rx_program* prog, const uint8_t* d_bytes, int64_t length
     // a compiled circuit of at most kLongChunkMaxState words, default chunking:
     // the string as circuit chunks (each an affine map of the state words)
     const int64_t circuit_need = chunks == 0 && length <= (int64_t(1) << 40) ? long_chunk_work_bytes(P, length) : -1;
+    LongGate gate;
     if (circuit_need >= 0 && (size_t)circuit_need <= work_bytes) {
-        if (int e = launch_long_chunks(P, d_bytes, length, d_work, d_out, stream)) return hip_fail(e, "kernel launch");
+        if (int rc = long_spans(P, d_bytes, length, chunks, d_out, nullptr, &gate, stream)) return rc;
+        if (int e = launch_long_chunks(P, d_bytes, length, d_work, d_out, gate, stream)) return hip_fail(e, "kernel launch");
         return RX_OK;
     }
     int64_t C, cl;
@@ -354,7 +423,8 @@ int rx_match_long(const rx_program* prog, const uint8_t* d_bytes, int64_t length
     if (work_bytes < need)
         return fail(RX_EINVAL, "workspace holds " + std::to_string(work_bytes) + " bytes; this run needs " +
                                    std::to_string(need) + " (rx_match_long_workspace)");
-    return match_long_run(P, d_bytes, length, C, cl, d_work, d_out, stream);
+    if (int rc = long_spans(P, d_bytes, length, chunks, d_out, nullptr, &gate, stream)) return rc;
+    return match_long_run(P, d_bytes, length, C, cl, d_work, d_out, gate, stream);
     RX_GUARD_END
 }
 
@@ -378,7 +448,9 @@ int rx_match_long_noalloc(const rx_program* prog, const uint8_t* d_bytes, int64_
     }
     void* work = nullptr;
     if (int e = long_scratch(&work)) return hip_fail(e, "device address of the static workspace");
-    return match_long_run(P, d_bytes, length, C, cl, work, d_out, stream);
+    LongGate gate;
+    if (int rc = long_spans(P, d_bytes, length, chunks, d_out, nullptr, &gate, stream)) return rc;
+    return match_long_run(P, d_bytes, length, C, cl, work, d_out, gate, stream);
     RX_GUARD_END
 }
 
@@ -404,11 +476,15 @@ int rx_match_first_long(const rx_program* prog, const uint8_t* d_bytes, int64_t 
         if (e) return hip_fail(e, "kernel launch");
         return RX_OK;
     }
+    LongGate gate;
+    if (int rc = long_spans(P, d_bytes, length, chunks, nullptr, d_first, &gate, stream)) return rc;
     LaunchArgs a;
     if (int rc = make_launch_args(P, d_bytes ? d_bytes : static_cast<const uint8_t*>(d_work),
                                   static_cast<const int64_t*>(d_work), long_rows(P, C),
                                   static_cast<uint8_t*>(d_work), stream, &a))
         return rc;
+    a.skip = gate.slot;
+    a.skip_id = gate.id;
     a.offsets = nullptr;
     a.out = nullptr;
     a.rows_out = static_cast<uint32_t*>(d_work);
@@ -418,7 +494,7 @@ int rx_match_first_long(const rx_program* prog, const uint8_t* d_bytes, int64_t 
     a.rows_per_chunk = P->L + 1;
     e = P->W <= kLaneMaxWords ? launch_lane(a) : launch_wave(a);
     if (e) return hip_fail(e, "kernel launch (rows)");
-    e = launch_compose_first(a.rows_out, a.first_pos, C, cl, P->L + 1, P->W, d_first, stream);
+    e = launch_compose_first(a.rows_out, a.first_pos, C, cl, P->L + 1, P->W, d_first, gate, stream);
     if (e) return hip_fail(e, "kernel launch (composition)");
     return RX_OK;
     RX_GUARD_END
@@ -470,30 +546,29 @@ int rx_match_first_fixed(const rx_program* prog, const uint8_t* d_bytes, int64_t
     if (!P->dev) return fail(RX_ENOTUPLOADED, "program has not been uploaded (rx_program_upload)");
     if (n == 0) return RX_OK;
     int e;
+    LaunchArgs a;
+    if (int rc = make_launch_args(P, d_bytes ? d_bytes : reinterpret_cast<const uint8_t*>(d_first),
+                                  reinterpret_cast<const int64_t*>(d_first), n,
+                                  reinterpret_cast<uint8_t*>(d_first), stream, &a))
+        return rc;
+    a.offsets = nullptr;
+    a.stride = length;
+    a.out = nullptr;
+    a.first_pos = d_first;
+    const bool sliced_ok = jit_first_ready(P) && length > 0 && (length % 16) == 0 && length <= (1 << 26) &&
+                           (reinterpret_cast<uintptr_t>(d_bytes) & 15) == 0;
     if (P->nullable) {
         e = launch_fill_i64(d_first, n, 0, stream);   // the empty prefix is accepted
-    } else if (jit_first_ready(P) && length > 0 && (length % 16) == 0 && length <= (1 << 26) &&
-               (reinterpret_cast<uintptr_t>(d_bytes) & 15) == 0) {
+    } else if (sliced_ok ? spans_over_sliced(P, a) : spans_ok(P, a)) {
+        e = launch_spans_fill(a);
+        if (!e) e = run_spans(P, a);
+    } else if (sliced_ok) {
         e = launch_sliced_first(P, d_bytes, length, n, d_first, stream);
+    } else if (P->W <= kLaneMaxWords) {
+        e = launch_lane(a);
     } else {
-        LaunchArgs a;
-        if (int rc = make_launch_args(P, d_bytes ? d_bytes : reinterpret_cast<const uint8_t*>(d_first),
-                                      reinterpret_cast<const int64_t*>(d_first), n,
-                                      reinterpret_cast<uint8_t*>(d_first), stream, &a))
-            return rc;
-        a.offsets = nullptr;
-        a.stride = length;
-        a.out = nullptr;
-        a.first_pos = d_first;
-        if (spans_ok(P, a)) {
-            e = launch_spans_fill(a);
-            if (!e) e = launch_spans(a);
-        } else if (P->W <= kLaneMaxWords) {
-            e = launch_lane(a);
-        } else {
-            if (P->W > kWaveMaxWords) return fail(RX_ETOOBIG, "the wavefront kernel holds sets of at most 128 words");
-            e = launch_wave(a);
-        }
+        if (P->W > kWaveMaxWords) return fail(RX_ETOOBIG, "the wavefront kernel holds sets of at most 128 words");
+        e = launch_wave(a);
     }
     if (e) return hip_fail(e, "kernel launch");
     return RX_OK;
@@ -516,7 +591,7 @@ int rx_match_first(const rx_program* prog, const uint8_t* d_bytes, const int64_t
     int e;
     if (spans_ok(P, a)) {
         e = launch_spans_fill(a);
-        if (!e) e = launch_spans(a);
+        if (!e) e = run_spans(P, a);
     } else if (P->W <= kLaneMaxWords) {
         e = launch_lane(a);
     } else {
@@ -558,9 +633,9 @@ int rx_match_fixed_ex(const rx_program* prog, const uint8_t* d_bytes, int64_t le
     // many short ones fill the chip better 32 strings to a lane.
     const bool chunks_ok = jit_chunks_ready(P) && length > 0;
     const bool auto_chunks = chunks_ok && (length >= 32768 || n <= 4096);
-    if (variant == RX_VARIANT_AUTO && !auto_chunks && !sliced_ok && spans_ok(P, a)) {
+    if (variant == RX_VARIANT_AUTO && !auto_chunks && (sliced_ok ? spans_over_sliced(P, a) : spans_ok(P, a))) {
         int e = launch_spans_fill(a);
-        if (!e) e = launch_spans(a);
+        if (!e) e = run_spans(P, a);
         if (e) return hip_fail(e, "kernel launch (spans)");
         return RX_OK;
     }

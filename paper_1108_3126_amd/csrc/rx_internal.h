@@ -221,6 +221,7 @@ struct LaunchArgs {
     const int64_t* skip = nullptr;
     int64_t skip_id = 0;
     int32_t prefix = -1;   // the program's span_prefix
+    int64_t* undone = nullptr;   // one long string over spans: see LongGate
 };
 int launch_lane(const LaunchArgs& a);
 // A searched program (span_prefix >= 0) over equal spans of bytes:
@@ -228,6 +229,18 @@ int launch_lane(const LaunchArgs& a);
 // those of the strings that match.
 int launch_spans_fill(const LaunchArgs& a);
 int launch_spans(const LaunchArgs& a);
+// One long string over spans, before the chunk-parallel kernels: a layout slot
+// {id, 0, 0, undone}; a thread that outlives its span by more than
+// kSpanLongLimit bytes (or a circuit's region) sets `undone` instead of being
+// followed.  The chunk-parallel kernels given the gate do nothing where the
+// slot still holds the id and nothing undone; where a later call has taken the
+// slot, they run (same result).
+struct LongGate {
+    const int64_t* slot = nullptr;
+    int64_t id = 0;
+};
+constexpr int64_t kSpanLongLimit = 4096;
+int launch_span_long_begin(const LongGate& gate, uint8_t* out, int64_t* first, void* stream);
 // Equal-length consecutive strings for rx_match (rx_kernels.hip): the slot of
 // call `id` in a static per-device array of kLayoutSlots slots of four int64
 // {id, length, first offset, flaw}; launch_layout_check fills it on `stream`
@@ -251,11 +264,22 @@ bool jit_chunks_ready(const Program* P);
 constexpr int kLongChunkMaxState = 31;   // a state as bits 0 .. NS - 1 of a word, the accept bit 31
 int64_t long_chunk_work_bytes(const Program* P, int64_t length);
 int launch_long_chunks(const Program* P, const uint8_t* bytes, int64_t length, void* work, uint8_t* out,
-                       void* stream);
+                       const LongGate& gate, void* stream);
 int launch_sliced_chunks(const Program* P, const uint8_t* bytes, int64_t length, int64_t n, uint8_t* out,
                          void* stream);
 // (suffix_slot: the state word of a searched program's suffix leaf, or -1)
-std::string jit_step_source(const Program& P, int* n_state, int* n_ops, int* suffix_slot = nullptr);
+// (rest: rx_step_rest, the step without the leaves that are always live; empty
+// where a word starts as ones)
+std::string jit_step_source(const Program& P, int* n_state, int* n_ops, int* suffix_slot = nullptr,
+                            std::string* rest = nullptr);
+// The circuit over equal spans of bytes, for searched programs (span_prefix)
+// of at most kSpanMaxState words: results as launch_spans; with `undone`, a
+// string that a thread outlives the region in is reported there instead of
+// followed.
+constexpr int kSpanMaxState = 64;
+std::string jit_spans_source(const Program& P);
+bool jit_spans_ready(const Program* P);
+int launch_span_circuit(const Program* P, const LaunchArgs& a);
 std::string jit_full_source(const Program& P, int* n_state, int* n_ops);
 int jit_compile(Program* P, const char* arch);
 void jit_free(Program* P);
@@ -314,9 +338,9 @@ int launch_sliced_fixed(const Program* P, const uint8_t* bytes, int64_t length, 
 int launch_wave(const LaunchArgs& a);
 // rx_match_long, second pass: one workgroup applies the chunks' relations in order
 int launch_compose(const uint32_t* rows, int64_t chunks, int32_t rpc, int32_t W, int32_t L, int32_t suffix_any,
-                   uint8_t* out, void* stream);
+                   uint8_t* out, const LongGate& gate, void* stream);
 int launch_compose_first(const uint32_t* rows, const int64_t* fp, int64_t chunks, int64_t cl, int32_t rpc,
-                         int32_t W, int64_t* out, void* stream);
+                         int32_t W, int64_t* out, const LongGate& gate, void* stream);
 const char* hip_error_string(int err);
 int launch_stream_copy(void* dst, const void* src, int64_t bytes, void* stream);
 int hip_current_device(int* dev);

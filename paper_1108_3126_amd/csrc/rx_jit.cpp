@@ -31,6 +31,7 @@
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
+#include <future>
 #include <mutex>
 #include <sstream>
 #include <string>
@@ -209,7 +210,7 @@ std::array<uint64_t, 4> label_set(const Program& P, int p) {
 
 // Generates the step function (device/host neutral C++): rx_step(s, acc, b0..b7)
 // plus the initial state.  Fills n_state (state words) and n_ops.
-std::string jit_step_source(const Program& P, int* n_state, int* n_ops, int* suffix_slot) {
+std::string jit_step_source(const Program& P, int* n_state, int* n_ops, int* suffix_slot, std::string* rest) {
     const int nt = P.n_tree;
     std::vector<char> nu(nt, 0);
     for (int p = nt - 1; p >= 0; --p) {
@@ -255,8 +256,9 @@ std::string jit_step_source(const Program& P, int* n_state, int* n_ops, int* suf
         }
     };
     number();
-    for (;;) {
-        Emitter E;
+    // The step's signals: out (bottom-up) and in (top-down) of every node.
+    // ones: the value of the leaves that are constant all-ones.
+    auto signals = [&](Emitter& E, const V& ones, std::vector<V>& out, std::vector<V>& in) {
         E.code << "    const u32 nb0 = ~b0, nb1 = ~b1, nb2 = ~b2, nb3 = ~b3, nb4 = ~b4, nb5 = ~b5, nb6 = ~b6, nb7 = ~b7;\n";
         Decoder D(E);
         // one decoded mask per distinct label
@@ -277,9 +279,10 @@ std::string jit_step_source(const Program& P, int* n_state, int* n_ops, int* suf
             lab[x] = seen_vals[found];
         }
         auto state = [&](int x) {
-            return slot[x] == kOne ? E.one : slot[x] < 0 ? E.zero : V{-1, "s[" + std::to_string(slot[x]) + "]"};
+            return slot[x] == kOne ? ones : slot[x] < 0 ? E.zero : V{-1, "s[" + std::to_string(slot[x]) + "]"};
         };
-        std::vector<V> out(nt, E.zero), in(nt, E.zero);
+        out.assign(nt, E.zero);
+        in.assign(nt, E.zero);
         for (int p = nt - 1; p >= 0; --p) {
             const int a = P.c0[p], b = P.c1[p];
             switch (P.kind[p]) {
@@ -305,6 +308,31 @@ std::string jit_step_source(const Program& P, int* n_state, int* n_ops, int* suf
             default: break;
             }
         }
+    };
+    // The new state (each word once) and the accept bit, after every value is
+    // computed.  An update that is another word as it was (a leaf that any
+    // byte moves on) is read before any word changes.
+    auto commit = [&](const std::vector<V>& out, const std::vector<V>& in) {
+        std::ostringstream olds, tail;
+        auto value = [&](const V& v, const std::string& name) {
+            if (v.c >= 0 || v.n.rfind("s[", 0) != 0) return Emitter::str(v);
+            olds << "    const u32 " << name << " = " << v.n << ";\n";
+            return name;
+        };
+        std::vector<char> done(ns > 0 ? ns : 1, 0);
+        for (int r = 0; r < P.L; ++r) {
+            const int x = P.leaf_node[r];
+            if (slot[x] < 0 || done[slot[x]]) continue;
+            done[slot[x]] = 1;
+            tail << "    s[" << slot[x] << "] = " << value(in[x], "o" + std::to_string(slot[x])) << ";\n";
+        }
+        tail << "    acc = " << value(out[0], "oacc") << ";\n";
+        return olds.str() + tail.str();
+    };
+    for (;;) {
+        Emitter E;
+        std::vector<V> out, in;
+        signals(E, E.one, out, in);
         // refine: (class, update) -> class
         std::vector<int> ngrp(P.m, -1), nkind;
         std::unordered_map<std::string, int> cls;
@@ -358,35 +386,20 @@ std::string jit_step_source(const Program& P, int* n_state, int* n_ops, int* suf
             number();
             continue;
         }
-        // Commit the new state after every value is computed.  An update that
-        // is another word as it was (a leaf that any byte moves on) is read
-        // before any word changes.
-        std::ostringstream olds, tail;
-        auto value = [&](const V& v, const std::string& name) {
-            if (v.c >= 0 || v.n.rfind("s[", 0) != 0) return Emitter::str(v);
-            olds << "    const u32 " << name << " = " << v.n << ";\n";
-            return name;
-        };
-        std::vector<char> done(ns > 0 ? ns : 1, 0);
-        for (int r = 0; r < P.L; ++r) {
-            const int x = P.leaf_node[r];
-            if (slot[x] < 0 || done[slot[x]]) continue;
-            done[slot[x]] = 1;
-            tail << "    s[" << slot[x] << "] = " << value(in[x], "o" + std::to_string(slot[x])) << ";\n";
-        }
-        tail << "    acc = " << value(out[0], "oacc") << ";\n";
         std::ostringstream src;
         src << "#define RX_NS " << (ns > 0 ? ns : 1) << "\n";
         src << "__device__ __forceinline__ void rx_step(u32 (&s)[RX_NS], u32& acc, u32 b0, u32 b1, u32 b2, u32 b3,"
                " u32 b4, u32 b5, u32 b6, u32 b7) {\n";
-        src << E.code.str() << olds.str() << tail.str() << "}\n";
+        src << E.code.str() << commit(out, in) << "}\n";
+        std::vector<char> done(ns > 0 ? ns : 1, 0);
+        bool starts_zero = true;
         src << "__device__ __forceinline__ void rx_init(u32 (&s)[RX_NS], u32& acc) {\n";
         for (int k = 0; k < (ns > 0 ? ns : 1); ++k) src << "    s[" << k << "] = 0u;\n";
-        std::fill(done.begin(), done.end(), 0);
         for (int r = 0; r < P.L; ++r) {
             const int x = P.leaf_node[r];
             if (slot[x] >= 0 && !done[slot[x]] && is_first(r)) {
                 done[slot[x]] = 1;
+                starts_zero = false;
                 src << "    s[" << slot[x] << "] = 0xffffffffu;\n";
             }
         }
@@ -396,6 +409,23 @@ std::string jit_step_source(const Program& P, int* n_state, int* n_ops, int* suf
         if (suffix_slot) {
             const int suf = search_suffix_leaf(P);
             *suffix_slot = suf >= 0 && slot[suf] >= 0 ? slot[suf] : -1;
+        }
+        if (rest) {
+            // The same step without the leaves that are always live (First's,
+            // in a searched program): what becomes of the threads begun
+            // before.  Only where every word starts as zero, so that a cleared
+            // word is a string's start.
+            rest->clear();
+            if (starts_zero && ns > 0) {
+                Emitter E2;
+                std::vector<V> out2, in2;
+                signals(E2, E2.zero, out2, in2);
+                std::ostringstream r;
+                r << "__device__ __forceinline__ void rx_step_rest(u32 (&s)[RX_NS], u32& acc, u32 b0, u32 b1, u32 b2, "
+                     "u32 b3, u32 b4, u32 b5, u32 b6, u32 b7) {\n"
+                  << E2.code.str() << commit(out2, in2) << "}\n";
+                *rest = r.str();
+            }
         }
         return src.str();
     }
@@ -753,7 +783,9 @@ extern "C" __global__ __launch_bounds__(64) void rx_sliced_chunks(const unsigned
 extern "C" __global__ __launch_bounds__(64) void rx_long_chunks(const unsigned char* __restrict__ bytes,
                                                                 long long length, long long Lc,
                                                                 u32* __restrict__ seg_maps,
-                                                                u32* __restrict__ chunk_maps) {
+                                                                u32* __restrict__ chunk_maps,
+                                                                const long long* __restrict__ gate, long long id) {
+    if (gate && gate[0] == id && gate[3] == 0) return;   // the span form has the result
     const long long g = blockIdx.x;
     const int lane = threadIdx.x;
     const long long base = g * 2048 * Lc;
@@ -798,7 +830,9 @@ extern "C" __global__ __launch_bounds__(64) void rx_long_chunks(const unsigned c
 // The G segments' maps in order (one wavefront: lane l composes a run of
 // consecutive segments, then the lanes in order), applied to the start state.
 extern "C" __global__ __launch_bounds__(64) void rx_long_compose(const u32* __restrict__ seg_maps, long long G,
-                                                                 unsigned char* __restrict__ out) {
+                                                                 unsigned char* __restrict__ out,
+                                                                 const long long* __restrict__ gate, long long id) {
+    if (gate && gate[0] == id && gate[3] == 0) return;
     const int lane = threadIdx.x;
     const long long per = (G + 63) / 64, g0 = lane * per, g1 = g0 + per < G ? g0 + per : G;
     u32 f[RX_M];
@@ -1622,6 +1656,384 @@ extern "C" __global__ __launch_bounds__(64 * RX_SPEC_WAVES) void rx_planes_spec(
 }
 )RX";
 
+// A searched program's circuit over equal spans of the strings' bytes (the
+// bit-sliced form of rx_spans.h).  A region of 2,048 slots of 16 consecutive
+// bytes is one wavefront's: lane l holds slots 32 l .. 32 l + 31 as the bits of
+// every word.  Every slot runs from the empty state (a searched program's
+// First leaves are constants), a string's start clears its bits, and what is
+// left at a slot's end runs on over the following slots' bytes -- their planes
+// shifted by whole slots -- without starting new threads, less the threads
+// that those slots hold themselves at their ends.  The last lane's 32 slots
+// are there for that alone: the next region begins with them.  So the text is
+// read once, in whole lines, whatever the strings' lengths.  An accept is
+// noted where it first appears in a slot and string; the string is found by
+// counting start bits.
+//
+// 16 bytes a slot: their planes (32 KB) and two words per position beside them
+// are a quarter of a compute unit's LDS, so every SIMD has a wavefront; what is
+// left past a slot lives five bytes or so in the longest of 2,016 slots, so
+// about a third more steps than bytes.  One wavefront per SIMD leaves it room
+// for the next region's bytes in registers (128 of them).  10^6 lines (120
+// MB), 43 words: 100 us for the kernel, half of it vector instructions (6,300
+// a region: 1,280 for the transposes, 170 a position), a third waiting (the
+// first region's bytes, the search for its first string); 236 us over the
+// tables.  64 MB of 256-byte strings, 17 words: 38 us; 99 us in the skewed
+// kernel, which has 123 workgroups then.
+const char* kSpanKernelSource = R"RX(
+typedef unsigned int rx_v4 __attribute__((ext_vector_type(4)));
+typedef long long i64;
+#define RX_REGION (2016 * 16)   // bytes of a region's own slots
+#define RX_WINDOW (2048 * 16)   // with the last lane's
+
+// One wavefront is the whole workgroup and its LDS accesses run in order, so
+// the compiler's order is all that is needed between them (a barrier would
+// also wait for the next region's loads).
+__device__ __forceinline__ void rx_lds_order() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
+
+struct rx_span_text {
+    const unsigned char* bytes;
+    const i64* offsets;   // or NULL: string i is bytes[i * stride, (i + 1) * stride)
+    i64 stride, n;
+    unsigned char* out;   // 0 before the launch, or
+    i64* first;           // -1 before the launch (earliest accepts wanted)
+    const u32 *first_row, *follow, *bytemask;   // the program's tables (threads that outlive the last lane)
+    int prefix;
+    const i64* skip;      // rx_match's layout slot: nothing to do when it holds skip_id and no flaw
+    i64 skip_id;
+    i64* undone;          // not NULL: set, instead of following a thread past the last lane
+};
+
+// The first i in [0, n] with offsets[i] >= v, or n + 1.
+__device__ i64 rx_lower_bound(const i64* offsets, i64 n, i64 v, int lane) {
+    i64 lo = 0, hi = n + 1;
+    while (hi - lo > 64) {
+        const i64 step = (hi - lo + 63) / 64, i = lo + lane * step;
+        const int k = __popcll(__ballot(i < hi && offsets[i] < v));
+        if (k == 0) return lo;
+        const i64 top = lo + k * step;
+        lo += (k - 1) * step + 1;
+        if (top < hi) hi = top;
+    }
+    const i64 i = lo + lane;
+    return lo + __popcll(__ballot(i < hi && offsets[i] < v));
+}
+
+__device__ __forceinline__ void rx_span_accept(const rx_span_text& X, i64 string, i64 at) {
+    if (X.first) {
+        const i64 lo = X.offsets ? X.offsets[string] : string * X.stride;
+        atomicMin((unsigned long long*)(X.first + string), (unsigned long long)(at + 1 - lo));
+    } else {
+        X.out[string] = 1;
+    }
+}
+
+// A slot's threads in table form (Def. 5.1 / 5.2), one lane: from the slot's
+// first byte (or its last string's) to the string's end.  For threads that
+// outlive the region's last lane.
+__device__ void rx_span_alone(const rx_span_text& X, i64 string, i64 from, i64 slot_end) {
+    const i64 lo = X.offsets ? X.offsets[string] : string * X.stride;
+    const i64 end = X.offsets ? X.offsets[string + 1] : lo + X.stride;
+    u32 A[RX_W], V[RX_W];   // the slot's threads; threads begun after it
+    for (int w = 0; w < RX_W; ++w) A[w] = V[w] = 0u;
+    for (i64 at = from > lo ? from : lo; at < end; ++at) {
+        const u32 c = X.bytes[at];
+        const bool in = at < slot_end;
+        u32 Y[RX_W], Z[RX_W];
+#pragma unroll
+        for (int w = 0; w < RX_W; ++w) {
+            const u32 f = X.first_row[w], pre = (X.prefix >> 5) == w ? 1u << (X.prefix & 31) : 0u;
+            const u32 m = X.bytemask[c * RX_W + w] & ~pre;
+            Y[w] = (in ? A[w] | f : A[w] & ~f & ~V[w]) & m;
+            Z[w] = in ? 0u : (V[w] | f) & m;
+            A[w] = V[w] = 0u;
+        }
+#pragma unroll
+        for (int w = 0; w < RX_W; ++w) {
+            u32 y = Y[w], z = Z[w];
+            while (y | z) {
+                const int b = __builtin_ctz(y | z);
+                const u32* row = X.follow + (w * 32 + b) * RX_W;
+                const u32 iy = 0u - ((y >> b) & 1u), iz = 0u - ((z >> b) & 1u);
+#pragma unroll
+                for (int v = 0; v < RX_W; ++v) {
+                    A[v] |= row[v] & iy;
+                    V[v] |= row[v] & iz;
+                }
+                y &= ~(1u << b);
+                z &= ~(1u << b);
+            }
+        }
+        if ((V[RX_W - 1] >> (RX_ACCEPT & 31)) & 1u) return;   // a later slot has the string's accept
+        if ((A[RX_W - 1] >> (RX_ACCEPT & 31)) & 1u) {
+            rx_span_accept(X, string, at);
+            return;
+        }
+        u32 left = 0u;
+#pragma unroll
+        for (int w = 0; w < RX_W; ++w) left |= A[w] & ~V[w] & ~X.first_row[w];
+        if (!in && left == 0u) return;
+    }
+}
+
+// Words of LDS: the planes of 16 positions (two 16-byte rows a lane each),
+// the start bits and the new accepts of each position.
+#define RX_SP_PLANES (16 * 8 * 64)
+extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void rx_spans(rx_span_text X) {
+    extern __shared__ u32 rx_sp[];
+    rx_v4* pl = reinterpret_cast<rx_v4*>(rx_sp);   // position t, half h, lane l at (2 t + h) 64 + l
+    u32* mk = rx_sp + RX_SP_PLANES;                // start bits: position t, lane l at 64 t + l
+    u32* ri = mk + 16 * 64;                        // new accepts, the same
+    u32* bm = rx_sp;                               // one bit per byte, before the planes are in place
+    const int lane = threadIdx.x;
+    const int up = lane < 63 ? lane + 1 : 63;
+    if (X.skip && X.skip[0] == X.skip_id && X.skip[3] == 0) return;
+    const i64 o0 = X.offsets ? X.offsets[0] : 0, oN = X.offsets ? X.offsets[X.n] : X.n * X.stride;
+    if (oN <= o0) return;
+    const int skew = (int)((unsigned long long)(X.bytes + o0) & 15ull);
+    const i64 regions = (oN - o0 + skew + RX_REGION - 1) / RX_REGION;
+    const i64 per = (regions + gridDim.x - 1) / gridDim.x, r0 = blockIdx.x * per;
+    const i64 r1 = r0 + per < regions ? r0 + per : regions;
+    if (r0 >= r1) return;
+    // Blocks past the text are read as its first block (every access holds a
+    // byte of the text; what is read there is cut off by the start bits).
+    const unsigned char* const head = X.bytes + o0 - skew;
+    const i64 last = (oN - 1 - (o0 - skew)) >> 4;   // the last block's number from there
+    rx_v4 win[32];
+    {
+        const i64 B = r0 * (RX_REGION / 16) + lane * 32;
+#pragma unroll
+        for (int j = 0; j < 32; ++j)
+            win[j] = *reinterpret_cast<const rx_v4*>(head + 16 * (B + j <= last ? B + j : 0));
+    }
+    i64 sid = X.offsets ? rx_lower_bound(X.offsets, X.n, o0 - skew + r0 * RX_REGION, lane) : 0;
+    i64 ahead[4];   // the first string starts of the region to come
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const i64 i = sid + 64 * k + lane;
+        ahead[k] = X.offsets ? X.offsets[i <= X.n ? i : X.n] : 0;
+    }
+    for (i64 r = r0; r < r1; ++r) {
+        const i64 S = o0 - skew + r * RX_REGION;
+        // -- where strings begin, one bit per byte of the window --
+        rx_lds_order();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pl[lane * 4 + k] = (rx_v4){0u, 0u, 0u, 0u};   // bm[0, 1024)
+        rx_lds_order();
+        i64 next = sid, seen = 0;   // the next region's first string; starts in this window
+        if (X.offsets) {
+            for (i64 base = sid;; base += 256) {
+                i64 v[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const i64 i = base + 64 * k + lane;
+                    if (base != sid) ahead[k] = X.offsets[i <= X.n ? i : X.n];
+                    v[k] = i <= X.n ? ahead[k] - S : RX_WINDOW;
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (v[k] < RX_WINDOW) atomicOr(&bm[(int)v[k] >> 5], 1u << ((int)v[k] & 31));
+                    next += __popcll(__ballot(v[k] < RX_REGION));
+                    seen += __popcll(__ballot(v[k] < RX_WINDOW));
+                }
+                if (~__ballot(v[3] < RX_WINDOW)) break;
+            }
+        } else {
+            const i64 i0 = S > 0 ? (S + X.stride - 1) / X.stride : 0;
+            for (i64 i = i0 + lane; i <= X.n && i * X.stride - S < RX_WINDOW; i += 64) {
+                const int v = (int)(i * X.stride - S);
+                atomicOr(&bm[v >> 5], 1u << (v & 31));
+            }
+        }
+        rx_lds_order();
+        u32 a[32];
+        int starts = 0;   // distinct starts in the lanes before this one, then with the region's own lanes
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            u32 w = bm[lane * 16 + k];
+            starts += __popc(w);
+            const i64 at = S + lane * 512 + 32 * k;   // outside the text no thread lives past its byte
+            if (at + 32 > oN) w |= at >= oN ? ~0u : ~0u << (int)(oN - at);
+            if (at < o0) w |= (1u << (int)(o0 - at)) - 1u;   // o0 - at = skew < 16
+            a[2 * k] = w & 0xffffu;
+            a[2 * k + 1] = w >> 16;
+        }
+        const int own = starts;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int v = __shfl_up(starts, d, 64);
+            if (lane >= d) starts += v;
+        }
+        const bool exact = !X.offsets || __shfl(starts, 63, 64) == (int)seen;   // no two strings begin at one byte
+        starts -= own;
+        rx_transpose32(a);
+        rx_lds_order();
+#pragma unroll
+        for (int t = 0; t < 16; ++t) mk[t * 64 + lane] = a[t];
+        const u32 m0 = a[0];
+        // -- bit planes --
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            u32 x[32];
+#pragma unroll
+            for (int j = 0; j < 32; ++j) x[j] = win[j][q];
+            rx_transpose32(x);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                pl[(4 * q + i) * 128 + lane] = (rx_v4){x[8 * i], x[8 * i + 1], x[8 * i + 2], x[8 * i + 3]};
+                pl[(4 * q + i) * 128 + 64 + lane] = (rx_v4){x[8 * i + 4], x[8 * i + 5], x[8 * i + 6], x[8 * i + 7]};
+            }
+        }
+        if (r + 1 < r1) {   // the next region's bytes and starts, on their way while this one runs
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const i64 i = next + 64 * k + lane;
+                ahead[k] = X.offsets ? X.offsets[i <= X.n ? i : X.n] : 0;
+            }
+            const i64 B = (r + 1) * (RX_REGION / 16) + lane * 32;
+#pragma unroll
+            for (int j = 0; j < 32; ++j)
+                win[j] = *reinterpret_cast<const rx_v4*>(head + 16 * (B + j <= last ? B + j : 0));
+        }
+        rx_lds_order();
+        // -- the slots --
+        u32 s[RX_NS], fin[RX_NS], acc = 0u, any = 0u;
+#pragma unroll
+        for (int k = 0; k < RX_NS; ++k) s[k] = 0u;
+        {
+            // (a string's start clears the words before its first byte: with
+            // the update of the byte before, in the same instructions)
+            u32 m = mk[lane];
+            rx_v4 lo = pl[lane], hi = pl[64 + lane];
+#pragma clang loop unroll_count(4)
+            for (int t = 0; t < 16; ++t) {
+                const int tn = t < 15 ? t + 1 : 15;
+                const u32 mn = mk[tn * 64 + lane];
+                const rx_v4 ln = pl[tn * 128 + lane], hn = pl[tn * 128 + 64 + lane];
+                const u32 before = acc & ~m, keep = t < 15 ? ~mn : ~0u;
+                rx_step(s, acc, lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w);
+#pragma unroll
+                for (int k = 0; k < RX_NS; ++k) s[k] &= keep;
+                const u32 fresh = acc & ~before;
+                ri[t * 64 + lane] = fresh;
+                any |= fresh;
+                m = mn;
+                lo = ln;
+                hi = hn;
+            }
+        }
+        // -- what is left of each slot's threads --
+        const u32 m0up = __shfl(m0, up, 64);
+        const u32 alive = lane < 63 ? ~((m0 >> 1) | (m0up << 31)) & ~acc : 0u;
+        u32 left = 0u, late = 0u;   // late: slots whose threads accepted past them
+#pragma unroll
+        for (int k = 0; k < RX_NS; ++k) {
+            fin[k] = s[k];
+            s[k] &= alive;
+            left |= s[k];
+        }
+        if (lane == 63) any = 0u;   // the next region's
+        // the string that holds byte t of slot 32 lane + j
+        auto string_of = [&](int j, int t) -> i64 {
+            const i64 at = S + (32 * lane + j) * 16 + t;
+            if (!X.offsets) return X.n == 1 ? 0 : at / X.stride;
+            if (exact) {
+                int k = starts;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) k += __popc(mk[v * 64 + lane] & (v <= t ? (2u << j) - 1u : (1u << j) - 1u));
+                // the block's head before the first string counts as starts (see above)
+                return sid - 1 + k - (S < o0 && lane == 0 ? (int)(o0 - S) : 0);
+            }
+            i64 lo = sid - 1, hi = sid + seen;   // offsets[lo] <= at, offsets[hi] > at (or hi is past the window's)
+            while (hi - lo > 1) {
+                const i64 mid = (lo + hi) >> 1;
+                if (X.offsets[mid] <= at) lo = mid;
+                else hi = mid;
+            }
+            return lo;
+        };
+        for (int u = 0; __ballot(left != 0u) != 0ull; ++u) {
+            if ((u & 15) == 0) {
+                if (u == 31 * 16) {   // past the last lane: in table form, or not at all
+                    if (X.undone) {
+                        if (left) *X.undone = 1;
+                    } else {
+                        while (left) {
+                            const int j = __builtin_ctz(left);
+                            left &= left - 1;
+                            const i64 at = S + (32 * lane + j) * 16;
+                            rx_span_alone(X, string_of(j, 15), at, at + 16);
+                        }
+                    }
+                    break;
+                }
+                if (u > 0) {   // less what slot + u / 16 holds at its end
+                    left = 0u;
+#pragma unroll
+                    for (int k = 0; k < RX_NS; ++k) {
+                        const u32 f = __shfl(fin[k], up, 64);
+                        s[k] &= ~__builtin_amdgcn_alignbit(f, fin[k], u >> 4);
+                        left |= s[k];
+                    }
+                    if (__ballot(left != 0u) == 0ull) break;
+                }
+            }
+            const int t = u & 15, q = (u >> 4) + 1;
+            const u32 keep = ~__builtin_amdgcn_alignbit(mk[t * 64 + up], mk[t * 64 + lane], q);
+            const rx_v4 lo = pl[t * 128 + lane], hi = pl[t * 128 + 64 + lane];
+            const rx_v4 lu = pl[t * 128 + up], hu = pl[t * 128 + 64 + up];
+            u32 b = 0u;
+#pragma unroll
+            for (int k = 0; k < RX_NS; ++k) s[k] &= keep;
+            rx_step_rest(s, b, __builtin_amdgcn_alignbit(lu.x, lo.x, q), __builtin_amdgcn_alignbit(lu.y, lo.y, q),
+                         __builtin_amdgcn_alignbit(lu.z, lo.z, q), __builtin_amdgcn_alignbit(lu.w, lo.w, q),
+                         __builtin_amdgcn_alignbit(hu.x, hi.x, q), __builtin_amdgcn_alignbit(hu.y, hi.y, q),
+                         __builtin_amdgcn_alignbit(hu.z, hi.z, q), __builtin_amdgcn_alignbit(hu.w, hi.w, q));
+            left = 0u;
+            if (__ballot(b != 0u) != 0ull) {
+#pragma unroll
+                for (int k = 0; k < RX_NS; ++k) s[k] &= ~b;
+            }
+#pragma unroll
+            for (int k = 0; k < RX_NS; ++k) left |= s[k];
+            if (X.first) {
+                while (b) {
+                    const int j = __builtin_ctz(b);
+                    b &= b - 1;
+                    rx_span_accept(X, string_of(j, 15), S + (32 * lane + j) * 16 + 16 + u);
+                }
+            } else {
+                late |= b;
+            }
+        }
+        // -- accepts --
+        while (late) {
+            const int j = __builtin_ctz(late);
+            late &= late - 1;
+            rx_span_accept(X, string_of(j, 15), 0);
+        }
+        if (__ballot(any != 0u) != 0ull) {
+            u32 fr[16];
+#pragma unroll
+            for (int t = 0; t < 16; ++t) fr[t] = any ? ri[t * 64 + lane] : 0u;
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                u32 f = fr[t];
+                while (f) {
+                    const int j = __builtin_ctz(f);
+                    f &= f - 1;
+                    const i64 at = S + (32 * lane + j) * 16 + t;
+                    if (at >= o0 && at < oN) rx_span_accept(X, string_of(j, t), at);
+                }
+            }
+        }
+        sid = next;
+    }
+}
+)RX";
+
 // The plane-form source for a list of programs: program k's circuit as
 // struct RxProgk (its step and start state in namespace rxqk), the tick
 // template, a dispatch over the programs and the kernel.
@@ -1711,6 +2123,8 @@ struct JitKernel {
     bool first_words = false;
     hipFunction_t chunks = nullptr;   // chunk-parallel form (circuits of at most two words)
     hipFunction_t long_chunks = nullptr, long_compose = nullptr;   // one long string (at most 31 words)
+    hipModule_t span_mod = nullptr;
+    hipFunction_t spans = nullptr;    // a searched program over equal spans of bytes
     int dev = -1;
     int n_state = 0, n_ops = 0;
     std::string arch;
@@ -1740,6 +2154,18 @@ std::string jit_full_source(const Program& P, int* n_state, int* n_ops) {
     s << kChunkSource;
     s << kFixedKernelSource;
     s << kChunkKernelSource;
+    return s.str();
+}
+
+// The span form's source; empty where the program has none.
+std::string jit_spans_source(const Program& P) {
+    if (P.span_prefix < 0) return std::string();
+    int ns = 0;
+    std::string rest, step = jit_step_source(P, &ns, nullptr, nullptr, &rest);
+    if (rest.empty() || ns > kSpanMaxState) return std::string();
+    std::ostringstream s;
+    s << "typedef unsigned int u32;\n#define RX_W " << P.W << "\n#define RX_ACCEPT " << P.L << "\n"
+      << step << rest << kTransposeSource << kSpanKernelSource;
     return s.str();
 }
 
@@ -1972,6 +2398,21 @@ SelfCheckBatch selfcheck_batch(const Program& P, int64_t n, int64_t length) {
 // batch; a staged kernel whose bits differ from the table step is dropped.
 // Returns nonzero when the check itself could not run or the LDS-staged
 // kernel disagrees.
+// The kernel argument of rx_spans (rx_span_text in its source).
+struct SpanTextArg {
+    const uint8_t* bytes = nullptr;
+    const int64_t* offsets = nullptr;
+    int64_t stride = 0, n = 0;
+    uint8_t* out = nullptr;
+    int64_t* first = nullptr;
+    const uint32_t *first_row = nullptr, *follow = nullptr, *bytemask = nullptr;
+    int32_t prefix = -1;
+    const int64_t* skip = nullptr;
+    int64_t skip_id = 0;
+    int64_t* undone = nullptr;
+};
+constexpr unsigned kSpanLds = 4 * (16 * 8 * 64 + 2 * 16 * 64);
+
 int jit_selfcheck(const Program& P, JitKernel* K, hipFunction_t* const* staged, int n_staged,
                   hipFunction_t* offsets_twin, hipFunction_t* offsets_twin_w) {
     const int64_t n = 4096, length = 256;
@@ -2046,6 +2487,27 @@ int jit_selfcheck(const Program& P, JitKernel* K, hipFunction_t* const* staged, 
             }
         }
     }
+    // the span form, on the batch as fixed-length strings, both results (no
+    // tables yet: a thread that would need them is reported, and not checked)
+    for (int kind = 0; kind < 2 && !rc && K->spans; ++kind) {
+        SpanTextArg x;
+        x.bytes = d_bytes;
+        x.stride = length;
+        x.n = n;
+        (kind ? (void*&)x.first : (void*&)x.out) = kind ? (void*)d_first : (void*)d_out;
+        x.undone = d_slot + 3;
+        void* args[] = {&x};
+        int64_t undone = 0;
+        hipError_t r = hipMemsetAsync(kind ? (void*)d_first : (void*)d_out, kind ? 0xff : 0, kind ? 8 * (size_t)n : (size_t)n, st);
+        if (r == hipSuccess) r = hipMemsetAsync(d_slot + 3, 0, 8, st);
+        if (r == hipSuccess) r = hipModuleLaunchKernel(K->spans, 64, 1, 1, 64, 1, 1, kSpanLds, st, args, nullptr);
+        if (r == hipSuccess) r = hipStreamSynchronize(st);
+        if (r == hipSuccess) r = hipMemcpy(&undone, d_slot + 3, 8, hipMemcpyDeviceToHost);
+        if (r == hipSuccess && !kind) r = hipMemcpy(out.data(), d_out, (size_t)n, hipMemcpyDeviceToHost);
+        if (r == hipSuccess && kind) r = hipMemcpy(fp.data(), d_first, 8 * (size_t)n, hipMemcpyDeviceToHost);
+        if (r != hipSuccess) rc = -1;
+        else if (!undone && (kind ? fp != B.first : out != B.accept)) K->spans = nullptr;
+    }
     if (d_bytes) (void)hipFree(d_bytes);
     if (d_out) (void)hipFree(d_out);
     if (d_first) (void)hipFree(d_first);
@@ -2065,8 +2527,14 @@ int jit_compile(Program* P, const char* arch_in) {
     std::string arch;
     int dev = -1;
     if (int rc = jit_target(arch_in, &arch, &dev)) return rc;
-    std::vector<char> code;
-    if (int rc = jit_code(src, arch, &code)) return rc;
+    // the span form's module compiles beside the main one
+    const std::string span_src = jit_spans_source(*P);
+    std::vector<char> code, span_code;
+    std::future<int> span_rc;
+    if (!span_src.empty()) span_rc = std::async(std::launch::async, [&] { return jit_code(span_src, arch, &span_code); });
+    const int main_rc = jit_code(src, arch, &code);
+    const bool have_spans = !span_src.empty() && span_rc.get() == RX_OK;
+    if (main_rc) return main_rc;
     JitKernel* K = new JitKernel;
     K->arch = arch;
     K->n_state = ns;
@@ -2116,9 +2584,19 @@ int jit_compile(Program* P, const char* arch_in) {
             K->long_chunks = K->long_compose = nullptr;
             (void)hipGetLastError();
         }
-        if (e != hipSuccess) {
+        if (e == hipSuccess && have_spans &&
+            (hipModuleLoadData(&K->span_mod, span_code.data()) != hipSuccess ||
+             hipModuleGetFunction(&K->spans, K->span_mod, "rx_spans") != hipSuccess)) {
+            K->spans = nullptr;
+            (void)hipGetLastError();
+        }
+        auto unload = [K] {
+            if (K->span_mod) hipModuleUnload(K->span_mod);
             hipModuleUnload(K->mod);
             delete K;
+        };
+        if (e != hipSuccess) {
+            unload();
             return fail(RX_EHIP, std::string("hipModuleGetFunction: ") + hipGetErrorString(e));
         }
         // The staged kernels keep in-flight loads in registers the compiler
@@ -2149,13 +2627,11 @@ int jit_compile(Program* P, const char* arch_in) {
         // table step; one that gives other bits is dropped as well.
         const int sc = jit_selfcheck(*P, K, staged, kNumStaged, &off, &off_w);
         if (sc == -2) {
-            hipModuleUnload(K->mod);
-            delete K;
+            unload();
             return fail(RX_EJIT, "the bit-sliced kernel gives other bits than the table step on the check batch");
         }
         if (sc != 0) {
-            hipModuleUnload(K->mod);
-            delete K;
+            unload();
             return fail(RX_EHIP, "the run-time check of the bit-sliced kernels could not run");
         }
         if (!K->skew) off = nullptr;
@@ -2175,6 +2651,7 @@ int jit_compile(Program* P, const char* arch_in) {
 void jit_free(Program* P) {
     JitKernel* K = static_cast<JitKernel*>(P->jit);
     if (!K) return;
+    if (K->span_mod) hipModuleUnload(K->span_mod);
     if (K->mod) hipModuleUnload(K->mod);
     delete K;
     P->jit = nullptr;
@@ -2280,6 +2757,42 @@ int launch_sliced_fixed(const Program* P, const uint8_t* bytes, int64_t length, 
     return (int)hipModuleLaunchKernel(fn, (unsigned)grid, 1, 1, threads, 1, 1, lds, (hipStream_t)stream, args, nullptr);
 }
 
+bool jit_spans_ready(const Program* P) {
+    const JitKernel* K = static_cast<const JitKernel*>(P->jit);
+    return K && K->spans;
+}
+
+int launch_span_circuit(const Program* P, const LaunchArgs& a) {
+    const JitKernel* K = static_cast<const JitKernel*>(P->jit);
+    if (!K || !K->spans) return (int)hipErrorInvalidValue;
+    SpanTextArg x;
+    x.bytes = a.bytes;
+    x.offsets = a.offsets;
+    x.stride = a.stride;
+    x.n = a.n;
+    x.out = a.out;
+    x.first = a.first_pos;
+    x.first_row = a.first;
+    x.follow = a.follow;
+    x.bytemask = a.bytemask;
+    x.prefix = a.prefix;
+    x.skip = a.skip;
+    x.skip_id = a.skip_id;
+    x.undone = a.undone;
+    int cus = 0;
+    if (hip_cu_count(&cus) || cus <= 0) cus = 256;
+    // one wavefront per SIMD: its registers hold the next region's bytes, and
+    // four of them fill the LDS of a compute unit
+    int64_t grid = 4 * (int64_t)cus;
+    if (!a.offsets) {
+        const int64_t regions = (a.n * a.stride + 15) / (2016 * 16) + 1;
+        if (regions < grid) grid = regions;
+    }
+    void* args[] = {&x};
+    return (int)hipModuleLaunchKernel(K->spans, (unsigned)grid, 1, 1, 64, 1, 1, kSpanLds, (hipStream_t)a.stream, args,
+                                      nullptr);
+}
+
 // Chunk length (a multiple of 16) and segments of the long-string form: up to
 // about 2,048 segments of 2,048 chunks (two wavefronts per SIMD), chunks of
 // at least 16 bytes.
@@ -2302,7 +2815,7 @@ int64_t long_chunk_work_bytes(const Program* P, int64_t length) {
 }
 
 int launch_long_chunks(const Program* P, const uint8_t* bytes, int64_t length, void* work, uint8_t* out,
-                       void* stream) {
+                       const LongGate& gate, void* stream) {
     const JitKernel* K = static_cast<const JitKernel*>(P->jit);
     if (!K || !K->long_chunks || !K->long_compose) return (int)hipErrorInvalidValue;
     int64_t Lc, G;
@@ -2313,13 +2826,15 @@ int launch_long_chunks(const Program* P, const uint8_t* bytes, int64_t length, v
     void* w = work;
     void* cm = static_cast<uint8_t*>(work) + ((4 * G * (K->n_state + 1) + 255) & ~int64_t(255));
     void* o = out;
+    const void* gt = gate.slot;
+    long long gid = gate.id;
     if (G > 0) {
-        void* args[] = {&b, &len, &lc, &w, &cm};
+        void* args[] = {&b, &len, &lc, &w, &cm, &gt, &gid};
         if (hipError_t e = hipModuleLaunchKernel(K->long_chunks, (unsigned)G, 1, 1, 64, 1, 1, 0, (hipStream_t)stream,
                                                  args, nullptr))
             return (int)e;
     }
-    void* args2[] = {&w, &gg, &o};
+    void* args2[] = {&w, &gg, &o, &gt, &gid};
     return (int)hipModuleLaunchKernel(K->long_compose, 1, 1, 1, 64, 1, 1, 0, (hipStream_t)stream, args2, nullptr);
 }
 

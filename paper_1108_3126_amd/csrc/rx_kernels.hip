@@ -543,6 +543,9 @@ int launch_wave(const LaunchArgs& a) {
     return (int)hipGetLastError();
 }
 
+// the span form has the long string's result
+__device__ __forceinline__ bool long_done(const LongGate& g) { return g.slot && g.slot[0] == g.id && g.slot[3] == 0; }
+
 // Chunk-parallel matching, second pass: apply the chunks' relations in order.
 // S starts as row 0 (chunk 0 run from First); for chunk c the new set is the
 // union of the rows T_c[r] over the leaves r in S, because the byte step maps
@@ -551,7 +554,8 @@ int launch_wave(const LaunchArgs& a) {
 // workgroup; exits early when S is empty or holds an absorbing accept.
 __global__ __launch_bounds__(1024) void k_compose(const uint32_t* __restrict__ T, int64_t chunks, int32_t rpc,
                                                   int32_t W, int32_t L, int32_t suffix_any,
-                                                  uint8_t* __restrict__ out) {
+                                                  uint8_t* __restrict__ out, LongGate gate) {
+    if (long_done(gate)) return;
     __shared__ uint32_t S[kWaveMaxWords], N[kWaveMaxWords];
     const int tid = threadIdx.x, nt = blockDim.x;
     const int aw = L >> 5;
@@ -586,7 +590,9 @@ __global__ __launch_bounds__(1024) void k_compose(const uint32_t* __restrict__ T
 // current chunk is applied, so the loads' latency is off the chain.
 template <int W>
 __global__ __launch_bounds__(512) void k_compose_lane(const uint32_t* __restrict__ T, int64_t chunks, int32_t rpc,
-                                                      int32_t L, int32_t suffix_any, uint8_t* __restrict__ out) {
+                                                      int32_t L, int32_t suffix_any, uint8_t* __restrict__ out,
+                                                      LongGate gate) {
+    if (long_done(gate)) return;
     __shared__ uint32_t S[W], N[W];
     const int tid = threadIdx.x;
     const bool own = tid < rpc;
@@ -630,7 +636,8 @@ __global__ __launch_bounds__(512) void k_compose_lane(const uint32_t* __restrict
 // bytes up to its first accept, -1 if none).
 __global__ __launch_bounds__(1024) void k_compose_first(const uint32_t* __restrict__ T, const int64_t* __restrict__ FP,
                                                         int64_t chunks, int64_t cl, int32_t rpc, int32_t W,
-                                                        int64_t* __restrict__ out) {
+                                                        int64_t* __restrict__ out, LongGate gate) {
+    if (long_done(gate)) return;
     __shared__ uint32_t S[kWaveMaxWords], N[kWaveMaxWords];
     __shared__ unsigned long long best;
     const int tid = threadIdx.x, nt = blockDim.x;
@@ -679,16 +686,16 @@ __global__ __launch_bounds__(256) void k_stream_copy(const uint4* __restrict__ s
 }
 
 int launch_compose_first(const uint32_t* rows, const int64_t* fp, int64_t chunks, int64_t cl, int32_t rpc,
-                         int32_t W, int64_t* out, void* stream) {
+                         int32_t W, int64_t* out, const LongGate& gate, void* stream) {
     int threads = ((rpc + 63) / 64) * 64;
     if (threads > 1024) threads = 1024;
     hipLaunchKernelGGL(k_compose_first, dim3(1), dim3(threads), 0, (hipStream_t)stream, rows, fp, chunks, cl, rpc, W,
-                       out);
+                       out, gate);
     return (int)hipGetLastError();
 }
 
 int launch_compose(const uint32_t* rows, int64_t chunks, int32_t rpc, int32_t W, int32_t L, int32_t suffix_any,
-                   uint8_t* out, void* stream) {
+                   uint8_t* out, const LongGate& gate, void* stream) {
     int threads = ((rpc + 63) / 64) * 64;
     if (threads > 1024) threads = 1024;
     if (W <= kLaneMaxWords && rpc <= 512) {
@@ -696,7 +703,7 @@ int launch_compose(const uint32_t* rows, int64_t chunks, int32_t rpc, int32_t W,
 #define RX_COMPOSE_CASE(w)                                                                                        \
     case w:                                                                                                       \
         hipLaunchKernelGGL((k_compose_lane<w>), dim3(1), dim3(threads), 0, (hipStream_t)stream, rows, chunks, rpc, L, \
-                           suffix_any, out);                                                                      \
+                           suffix_any, out, gate);                                                                \
         return (int)hipGetLastError();
             RX_COMPOSE_CASE(1) RX_COMPOSE_CASE(2) RX_COMPOSE_CASE(3) RX_COMPOSE_CASE(4) RX_COMPOSE_CASE(5)
             RX_COMPOSE_CASE(6) RX_COMPOSE_CASE(7) RX_COMPOSE_CASE(8) RX_COMPOSE_CASE(9) RX_COMPOSE_CASE(10)
@@ -707,7 +714,7 @@ int launch_compose(const uint32_t* rows, int64_t chunks, int32_t rpc, int32_t W,
         }
     }
     hipLaunchKernelGGL(k_compose, dim3(1), dim3(threads), 0, (hipStream_t)stream, rows, chunks, rpc, W, L, suffix_any,
-                       out);
+                       out, gate);
     return (int)hipGetLastError();
 }
 

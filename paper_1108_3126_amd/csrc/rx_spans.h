@@ -41,7 +41,7 @@ struct SpanProg {             // a searched, non-nullable program's tables (Def.
 struct SpanOut {
     uint8_t* out;             // results (0 before the launch), or
     int64_t* first_pos;       // earliest accepts (-1 before the launch)
-    int32_t* undone;          // not NULL: a lane gives up after `limit` bytes past its span and sets it
+    int64_t* undone;          // not NULL: a lane gives up after `limit` bytes past its span and sets it
     int64_t limit;
 };
 

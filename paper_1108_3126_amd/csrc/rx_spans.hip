@@ -75,11 +75,26 @@ int launch_spans_fill(const LaunchArgs& a) {
     return (int)hipGetLastError();
 }
 
+namespace {
+__global__ void k_span_long_begin(int64_t* slot, int64_t id, uint8_t* out, int64_t* first) {
+    slot[1] = slot[2] = slot[3] = 0;
+    slot[0] = id;
+    if (first) *first = -1;
+    else *out = 0;
+}
+}  // namespace
+
+int launch_span_long_begin(const LongGate& gate, uint8_t* out, int64_t* first, void* stream) {
+    hipLaunchKernelGGL(k_span_long_begin, dim3(1), dim3(1), 0, (hipStream_t)stream, const_cast<int64_t*>(gate.slot),
+                       gate.id, out, first);
+    return (int)hipGetLastError();
+}
+
 int launch_spans(const LaunchArgs& a) {
     SpanArgs k;
     k.prog = {a.first, a.follow, a.bytemask, a.L, a.prefix};
     k.text = {a.bytes, a.offsets, a.stride, a.n};
-    k.out = {a.out, a.first_pos, nullptr, 0};
+    k.out = {a.out, a.first_pos, a.undone, kSpanLongLimit};
     k.skip = a.skip;
     k.skip_id = a.skip_id;
     int cus = 0;

@@ -186,3 +186,91 @@ def test_spans_in_the_server(dev, graph):
                 reqs.append((a, r, c, s, data, offs))
             for rid, (a, r, c, s, data, offs) in zip(ids, reqs):
                 np.testing.assert_array_equal(srv.wait(rid), oracle.match(a, r, c, s, data, offs))
+
+
+# -- the same over the compiled circuit (regions of 2,016 slots of 16 bytes) ----------------------------------------
+CIRCUIT_LENS = [0, 1, 15, 16, 17, 31, 33, 0, 0, 511, 512, 513, 700, 40_000, 5, 0, 32_255, 32_256, 32_257, 100]
+
+
+@pytest.mark.parametrize("pattern", [b"ab|ba+c", b"a.*b.*c.*d", b"(a|b)*cd", b"a{20}[bc]{30}d", b"a[^q]{600}b"])
+def test_circuit_spans_against_the_oracle(dev, pattern):
+    p, tree = _compile(pattern)
+    try:
+        p.jit()
+    except Exception as e:   # more state words than the circuit holds: the tables run
+        assert "state words" in str(e)
+    for skew in (0, 3, 16):
+        rng = np.random.default_rng([len(pattern), skew])
+        lens = np.concatenate([rng.permutation(CIRCUIT_LENS), rng.integers(0, 80, 3000), rng.permutation(CIRCUIT_LENS)])
+        rare = b".*" in pattern or b"^q" in pattern
+        data, offs = _ragged(rng, b"x" * 150 + b"aabcd" if rare else b"abcd", lens, skew)
+        _check(dev, p, tree, data, offs, f"circuit {pattern} skew {skew}")
+
+
+@pytest.mark.parametrize("seed,nodes", [(4, 40), (5, 120), (6, 200), (8, 300)])
+def test_circuit_spans_trees(dev, seed, nodes):
+    t = W.multi_programs(seed=700 + seed, count=1, lo=nodes, hi=nodes)[0]
+    p, tree = _compile(t)
+    p.jit()
+    rng = np.random.default_rng(nodes)
+    lens = np.concatenate([rng.integers(0, 200, 2500), [9000, 0, 1]])
+    offs = np.zeros(len(lens) + 1, np.int64)
+    np.cumsum(lens, out=offs[1:])
+    _check(dev, p, tree, W.zipf_bytes(rng, int(offs[-1])), offs, f"circuit nodes {nodes} {p.jit_stats()}")
+
+
+def test_circuit_spans_many_strings(dev):
+    """More regions than wavefronts; strings of one byte and empty ones (several begin at one byte)."""
+    from paper_1108_3126_amd import rx
+
+    p, tree = _compile(b"ab{3}c|ca{4}b")
+    q, _ = _compile(b"ab{3}c|ca{4}b")
+    p.jit()
+    rng = np.random.default_rng(3)
+    for lens, what in ((np.full(200_000, 3), "short"), (rng.integers(0, 2, 400_000), "bytes and empties"),
+                       (rng.integers(1, 2000, 60_000), "mixed")):
+        data, offs = _ragged(rng, b"abc", lens, 3)
+        d, o = torch.from_numpy(data).to(dev), torch.from_numpy(offs).to(dev)
+        print(what, flush=True)
+        np.testing.assert_array_equal(rx.match(p, d, o).cpu().numpy(), rx.match(q, d, o).cpu().numpy(), err_msg=what)
+        np.testing.assert_array_equal(rx.match_first(p, d, o).cpu().numpy(), rx.match_first(q, d, o).cpu().numpy(),
+                                      err_msg=what)
+
+
+@pytest.mark.parametrize("length,n,shift", [(1, 1000, 0), (100, 2001, 0), (48, 500, 1), (333, 700, 3), (70_001, 3, 0)])
+def test_circuit_spans_fixed_lengths(dev, length, n, shift):
+    from paper_1108_3126_amd import rx
+
+    p, tree = _compile(b"ab{2}c|c.a.b{4}")
+    p.jit()
+    rng = np.random.default_rng(length)
+    data = np.frombuffer(b"abc", np.uint8)[rng.integers(0, 3, n * length)]
+    buf = torch.zeros(n * length + 16, dtype=torch.uint8, device=dev)
+    d = buf[shift:shift + n * length]
+    d.copy_(torch.from_numpy(data))
+    want_first, want = _earliest(tree, data, np.arange(n + 1, dtype=np.int64) * length)
+    np.testing.assert_array_equal(rx.match_fixed(p, d, length, n).cpu().numpy(), want)
+    np.testing.assert_array_equal(rx.match_first_fixed(p, d, length, n).cpu().numpy(), want_first)
+
+
+@pytest.mark.parametrize("jit", [False, True])
+def test_long_string_with_a_thread_that_outlives_its_span(dev, jit):
+    """One long string: a thread begun near the start that lives to the end (the span kernels leave it to the
+    chunk-parallel ones), one that dies within the limit, and none; with and without an accept."""
+    from paper_1108_3126_amd import rx
+
+    p, tree = _compile(b"a[^q]*b|cde")
+    if jit:
+        p.jit()
+    base = np.full(200_000, ord("x"), np.uint8)
+    for edits in ((), ((100, b"a"),), ((100, b"a"), (199_999, b"b")), ((100, b"a"), (2_000, b"q"), (150_000, b"b")),
+                  ((100, b"a"), (50_000, b"q"), (150_000, b"cde")), ((5, b"b"), (31_998, b"cde")), ((65_533, b"a"), (65_600, b"b"))):
+        text = base.copy()
+        for at, w in edits:
+            text[at:at + len(w)] = np.frombuffer(w, np.uint8)
+        d = torch.from_numpy(text).to(dev)
+        want_first, want = _earliest(tree, text, np.array([0, text.size]))
+        print(jit, edits, flush=True)
+        assert int(rx.match_long(p, d).item()) == want[0]
+        assert int(rx.match_first_long(p, d).item()) == want_first[0]
+        assert int(rx.match_long(p, d, text.size, 50).item()) == want[0]
