@@ -181,6 +181,40 @@ __global__ __launch_bounds__(256) void k_lane(KArgs a) {
     }
 }
 
+// The first position in [q, hi) whose byte is not c, or hi: a wavefront looks at
+// 1,024 bytes at a time (aligned 16-byte blocks that hold a byte of the
+// string).  Every lane returns it.
+__device__ __forceinline__ int64_t run_end(const uint8_t* __restrict__ bytes, int64_t q, int64_t hi, uint32_t c, int lane) {
+    const int64_t skew = (int64_t)(reinterpret_cast<uintptr_t>(bytes) & 15);
+    for (int64_t base = ((q + skew) & ~int64_t(15)) - skew; base < hi; base += 1024) {
+        const int64_t at = base + 16 * lane;
+        int stop = 16;   // the first byte of the block that ends the run
+        if (at < hi) {
+            const uint4 v = *reinterpret_cast<const uint4*>(bytes + at);
+            const uint32_t x[4] = {v.x ^ c * 0x01010101u, v.y ^ c * 0x01010101u, v.z ^ c * 0x01010101u, v.w ^ c * 0x01010101u};
+#pragma unroll
+            for (int b = 15; b >= 0; --b)
+                if (at + b >= q && (at + b >= hi || ((x[b >> 2] >> (8 * (b & 3))) & 255u))) stop = b;
+        } else {
+            stop = 0;
+        }
+        const uint64_t ends = __ballot(stop < 16);
+        if (ends) {
+            const int l = __builtin_ctzll(ends);
+            const int64_t e = base + 16 * l + __builtin_amdgcn_readlane(stop, l);
+            return e < hi ? e : hi;
+        }
+    }
+    return hi;
+}
+
+// A set that a byte maps to itself stays as it is while that byte repeats (the
+// step depends on the set and the byte alone, Def. 5.1 / 5.2), so after two
+// equal bytes that leave it unchanged the wavefront kernels go on at the run's
+// end (run_end).  The large programs' step is a chain of dependent reads, about 1.1
+// us a byte on 26 words: 256 strings of 1,000 bytes, nearly all one run,
+// 1,146 us without.  The test is two compares a byte.
+//
 // One wavefront per string.  Lane j owns words j and j + 64 of the set.
 template <bool TABLES_IN_LDS, bool FIRST, bool ROWS>
 __global__ __launch_bounds__(1024) void k_wave(KArgs a) {
@@ -226,10 +260,13 @@ __global__ __launch_bounds__(1024) void k_wave(KArgs a) {
             if (sw & abit) pos = 0;
         }
         const int64_t skew = (int64_t)(reinterpret_cast<uintptr_t>(a.bytes) & 3);
-        for (int64_t base = ((lo + skew) & ~int64_t(3)) - skew; base < hi && res < 0 && pos < 0; base += 4) {
+        uint32_t last = 256u;   // the byte before
+        for (int64_t at = lo, base; at < hi && res < 0 && pos < 0;) {
+            base = ((at + skew) & ~int64_t(3)) - skew;
             const uint32_t word = *reinterpret_cast<const uint32_t*>(a.bytes + base);
-            const int b0 = lo > base ? (int)(lo - base) : 0;
+            const int b0 = (int)(at - base);
             const int b1 = hi - base < 4 ? (int)(hi - base) : 4;
+            at = base + 4;
             for (int b = b0; b < b1 && pos < 0; ++b) {
                 const uint32_t c = (word >> (8 * b)) & 255u;
                 const uint32_t X0 = own0 ? (S0 & M[c * W + lane]) : 0u;
@@ -262,12 +299,18 @@ __global__ __launch_bounds__(1024) void k_wave(KArgs a) {
                         }
                     }
                 }
+                const bool still = __ballot(((S0 ^ N0) | (S1 ^ N1)) != 0u) == 0ull;
                 S0 = N0;
                 S1 = N1;
                 if (FIRST) {
                     const uint32_t sw = (uint32_t)__builtin_amdgcn_readlane((int)(aw < 64 ? S0 : S1), aw & 63);
                     if (sw & abit) pos = base + b + 1 - lo;
                 }
+                if (still && c == last && pos < 0) {
+                    at = run_end(a.bytes, base + b + 1, hi, c, lane);
+                    break;
+                }
+                last = c;
             }
             const bool live = __ballot((S0 | S1) != 0) != 0;
             if (!live) { res = 0; break; }
@@ -338,10 +381,13 @@ __global__ __launch_bounds__(64 * WS) void k_wave_split(KArgs a) {
         const int64_t hi = a.offsets ? a.offsets[sid + 1] : lo + a.stride;
         int res = -1;
         const int64_t skew = (int64_t)(reinterpret_cast<uintptr_t>(a.bytes) & 3);
-        for (int64_t base = ((lo + skew) & ~int64_t(3)) - skew; base < hi && res < 0; base += 4) {
+        uint32_t last = 256u;   // the byte before
+        for (int64_t at = lo, base; at < hi && res < 0;) {
+            base = ((at + skew) & ~int64_t(3)) - skew;
             const uint32_t word = *reinterpret_cast<const uint32_t*>(a.bytes + base);
-            const int b0 = lo > base ? (int)(lo - base) : 0;
+            const int b0 = (int)(at - base);
             const int b1 = hi - base < 4 ? (int)(hi - base) : 4;
+            at = base + 4;
             for (int b = b0; b < b1; ++b) {
                 const uint32_t c = (word >> (8 * b)) & 255u;
                 const uint32_t X0 = own0 ? (S0 & M[c * W + lane]) : 0u;
@@ -377,6 +423,7 @@ __global__ __launch_bounds__(64 * WS) void k_wave_split(KArgs a) {
                 part[parity][wave][lane] = N0;
                 part[parity][wave][lane + 64] = N1;
                 __syncthreads();
+                const uint32_t O0 = S0, O1 = S1;
                 S0 = 0;
                 S1 = 0;
 #pragma unroll
@@ -385,6 +432,12 @@ __global__ __launch_bounds__(64 * WS) void k_wave_split(KArgs a) {
                     S1 |= part[parity][w][lane + 64];
                 }
                 parity ^= 1;
+                // (every wavefront holds the same set and takes the same way)
+                if (c == last && __ballot(((S0 ^ O0) | (S1 ^ O1)) != 0u) == 0ull) {
+                    at = run_end(a.bytes, base + b + 1, hi, c, lane);
+                    break;
+                }
+                last = c;
             }
             const bool live = __ballot((S0 | S1) != 0) != 0;
             if (!live) { res = 0; break; }

@@ -122,6 +122,7 @@ __global__ __launch_bounds__(256) void k_items(ItemKArgs a) {
     __shared__ int s_item;
     int loaded = -1;
     const int total = *a.n_items;
+    if ((int)blockIdx.x >= total) return;   // the workgroups before take every item
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(a.head, 1);
         __syncthreads();
@@ -198,6 +199,7 @@ __global__ __launch_bounds__(kSpanQueueThreads) void k_span_queue(SpanQueueArgs 
         }
     }
     int loaded = -1;
+    if (blockIdx.x >= total) return;   // the workgroups before take every item
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(a.head, 1);
         __syncthreads();
@@ -737,7 +739,7 @@ namespace {
 struct SideStream {
     std::mutex mu;
     hipStream_t stream = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr;
+    hipEvent_t fork = nullptr, started = nullptr, join = nullptr;
 };
 
 int side_stream(hipStream_t st, SideStream** out) {
@@ -753,9 +755,11 @@ int side_stream(hipStream_t st, SideStream** out) {
         SideStream* x = new SideStream;
         hipError_t e = hipStreamCreateWithFlags(&x->stream, hipStreamNonBlocking);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&x->fork, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&x->started, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&x->join, hipEventDisableTiming);
         if (e != hipSuccess) {
             if (x->fork) (void)hipEventDestroy(x->fork);
+            if (x->started) (void)hipEventDestroy(x->started);
             if (x->stream) (void)hipStreamDestroy(x->stream);
             delete x;
             return (int)e;
@@ -819,7 +823,10 @@ int launch_planes_multi(const PlaneMultiArgs& m) {
     SideStream* side = nullptr;
     if (int e = side_stream(st, &side)) return e;
     std::lock_guard<std::mutex> lk(side->mu);
-    const int gs = (int)((m.n + 255) / 256 < 1024 ? (m.n + 255) / 256 : 1024);
+    // A workgroup of the counting and scattering kernels clears and merges 8,192
+    // bins whatever it counts: 2,048 strings each (500,000 lines: 23 + 32 us
+    // with 1,024 workgroups of 488, 11 + 19 with 245).
+    const int gs = (int)((m.n + 2047) / 2048 < 1024 ? (m.n + 2047) / 2048 : 1024);
     hipLaunchKernelGGL(k_sort_clear, dim3((kSortBins + 255) / 256), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_sort_count, dim3(gs > 0 ? gs : 1), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(1024), 0, st, a);
@@ -838,6 +845,12 @@ int launch_planes_multi(const PlaneMultiArgs& m) {
     // length of the call; the planes and circuits of every other slab run
     // beside them.
     const int64_t R = kLongSlabs < S ? kLongSlabs : S;
+    // With many other slabs their plane kernel waits until the long slabs'
+    // circuits are next on their stream: it would else fill the compute units
+    // that those, with most of a unit's LDS each, need empty (16 programs,
+    // 500,000 lines 593 -> 580 us, 3 * 10^6 lines 1,545 -> 1,457 us; with few
+    // slabs the wait costs more: 20,000 lines 500 -> 505 us).
+    const bool ahead = S > 64;
     pa.r_lo = 0;
     pa.r_hi = R;
     hipLaunchKernelGGL(k_planes<true>, dim3((unsigned)(4 * R * (kSortBins / (4 * kGroupTicks) + 1))), dim3(256), 0, st,
@@ -845,10 +858,14 @@ int launch_planes_multi(const PlaneMultiArgs& m) {
     if (hipError_t e = hipGetLastError()) return (int)e;
     if (hipError_t e = hipEventRecord(side->fork, st)) return (int)e;
     if (hipError_t e = hipStreamWaitEvent(side->stream, side->fork, 0)) return (int)e;
+    if (ahead)
+        if (hipError_t e = hipEventRecord(side->started, side->stream)) return (int)e;
     if (int e = launch_planes_circuits(m.progs, m.n_progs, planes, a.slab_tick, a.info, res, S, 0, R, true,
                                        side->stream))
         return e;
     if (hipError_t e = hipEventRecord(side->join, side->stream)) return (int)e;
+    if (ahead)
+        if (hipError_t e = hipStreamWaitEvent(st, side->started, 0)) return (int)e;
     pa.r_lo = R;
     pa.r_hi = S;
     if (S > R)
@@ -867,9 +884,6 @@ int launch_planes_multi(const PlaneMultiArgs& m) {
     ga.out = m.out;
     const unsigned gx = (unsigned)((m.n + 255) / 256 < 8192 ? (m.n + 255) / 256 : 8192);
     hipLaunchKernelGGL(k_gather_out, dim3(gx), dim3(256), 0, st, ga);
-    // then the long slabs, once their circuits are done
-    if (hipError_t e = hipStreamWaitEvent(st, side->join, 0)) return (int)e;
-    hipLaunchKernelGGL(k_gather_long, dim3((unsigned)((R * kSlabStrings + 255) / 256)), dim3(256), 0, st, ga);
     // strings too long for a slab: table form, every program
     OverArgs o;
     o.info = a.info;
@@ -897,6 +911,9 @@ int launch_planes_multi(const PlaneMultiArgs& m) {
         if (words > max_lds_words) max_lds_words = words;
     }
     hipLaunchKernelGGL(k_items, dim3(m.item_grid), dim3(m.block_lines), 4 * (size_t)max_lds_words, st, k);
+    // then the long slabs, once their circuits are done
+    if (hipError_t e = hipStreamWaitEvent(st, side->join, 0)) return (int)e;
+    hipLaunchKernelGGL(k_gather_long, dim3((unsigned)((R * kSlabStrings + 255) / 256)), dim3(256), 0, st, ga);
     return (int)hipGetLastError();
 }
 
