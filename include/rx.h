@@ -381,8 +381,8 @@ int rx_match_ex(const rx_program* prog, const uint8_t* d_bytes, const int64_t* d
  * the sliced kernel runs (one lane advances 32 strings per instruction);
  * otherwise the table-form kernels run.  A searched program's strings run over
  * spans, as in rx_match, where that is faster: lengths and addresses that the
- * sliced kernel does not take, and fewer than 524288 strings of 64 bytes or
- * more.  Same results either way.
+ * sliced kernel does not take, and strings of 64 bytes or more that are fewer
+ * than 524288 or whose circuit fits no staged kernel.  Same results either way.
  * Errors: RX_EINVAL, RX_ENOTUPLOADED, RX_EHIP.
  */
 int rx_match_fixed(const rx_program* prog, const uint8_t* d_bytes, int64_t length, int64_t n, uint8_t* d_out,

@@ -198,31 +198,33 @@ bool spans_ok(const Program* P, const LaunchArgs& a) {
     return a.offsets || a.stride >= 20 || a.n >= ((int64_t)2 << 20) / (a.stride + 1);
 }
 // Spans over the compiled circuit or over the tables.  A circuit's wavefront
-// works through 32 KB whatever the text's size, so it begins at about 25 us;
+// works through 32 KB whatever the text's size, so it begins at about 20 us;
 // the tables begin at 13 us and take longer per byte, the more the wider the
-// sets.  Measured, lines of 120 bytes on average: one word, 100,000 lines 29
-// (circuit) and 20 us (tables), 200,000 31 and 29, 10^6 79 and 106; three
-// words, 50,000 lines 33 and 25, 100,000 36 and 38, 10^6 109 and 230; five
-// words, 50,000 lines 28 and 33.  With offsets the bytes are not known on the
-// host, so the strings' number stands for them.
+// sets.  Measured, lines of 120 bytes on average: one word, 100,000 lines 20
+// us (tables), 200,000 21 (circuit) and 29, 10^6 70 and 106; three words,
+// 50,000 lines 25 (tables), 100,000 26 (circuit) and 37, 10^6 97 and 230;
+// five words, 50,000 lines 33 (tables), 100,000 20 and 50.  With offsets the
+// bytes are not known on the host, so the strings' number stands for them.
 bool circuit_spans(const Program* P, const LaunchArgs& a) {
     if (!jit_spans_ready(P)) return false;
     const bool narrow = P->W <= 2;
-    if (a.offsets) return a.n >= (narrow ? 200000 : 65536);
-    return (double)a.n * (double)a.stride >= (narrow ? 24e6 : 8e6);
+    if (a.offsets) return a.n >= (narrow ? 100000 : 40000);
+    return (double)a.n * (double)a.stride >= (narrow ? 12e6 : 5e6);
 }
 
 // Fixed-length strings that the bit-sliced kernels take too.  A wavefront of
 // theirs holds 2,048 strings whatever their number, and the chip 512 such
 // sets: fewer strings take as long as a full chip's.  Spans take the time of
-// the bytes.  Measured, a 17-word circuit, strings of 256 bytes: 20,000 18
-// (spans) and 72 us (sliced), 250,000 41 and 73, 500,000 71 and 77, 600,000 84
-// and 85; of 64 bytes: 250,000 21 and 28, 600,000 39 and 31; of 16 bytes: 19
-// and 18, 20 and 18.
+// the bytes.  Measured, a 17-word circuit, strings of 256 bytes: 250,000 34
+// (spans) and 72 us (sliced), 500,000 58 and 76, 800,000 91 and 91; of 64
+// bytes: 250,000 20 and 27; of 16 bytes: 19 and 18.  A circuit whose staged
+// kernels would spill (55 words: 800,000 strings 142 and 197 us) takes spans
+// for any number.
 constexpr int64_t kSlicedStrings = 512 * 1024;
 bool spans_over_sliced(const Program* P, const LaunchArgs& a) {
-    if (!spans_ok(P, a) || a.stride < 64 || a.n >= kSlicedStrings) return false;
-    return jit_spans_ready(P) || (double)a.n * (double)a.stride < 8e6;
+    if (!spans_ok(P, a) || a.stride < 64) return false;
+    if (!jit_spans_ready(P)) return (double)a.n * (double)a.stride < 8e6 && a.n < kSlicedStrings;
+    return a.n < kSlicedStrings || jit_default_staging(P) != 5;
 }
 
 // No match everywhere, then the strings that match.

@@ -1674,11 +1674,15 @@ extern "C" __global__ __launch_bounds__(64 * RX_SPEC_WAVES) void rx_planes_spec(
 // left past a slot lives five bytes or so in the longest of 2,016 slots, so
 // about a third more steps than bytes.  One wavefront per SIMD leaves it room
 // for the next region's bytes in registers (128 of them).  10^6 lines (120
-// MB), 43 words: 100 us for the kernel, half of it vector instructions (6,300
-// a region: 1,280 for the transposes, 170 a position), a third waiting (the
+// MB), 43 words: 87 us for the kernel, 57% of it vector instructions (6,300
+// a region: 1,280 for the transposes, 170 a position), a fourth waiting (the
 // first region's bytes, the search for its first string); 236 us over the
-// tables.  64 MB of 256-byte strings, 17 words: 38 us; 99 us in the skewed
-// kernel, which has 123 workgroups then.
+// tables.  64 MB of 256-byte strings, 17 words: 34 us; 99 us in the skewed
+// kernel, which has 123 workgroups then.  A lane loads its 32 slots itself,
+// 512 bytes in a row: 64 lines a load, whose issue takes a quarter of the time
+// there; loading 64 consecutive blocks at a time and exchanging them through
+// LDS took that down to a sixth and as much time for the exchange (250,000 x
+// 256 bytes 36 -> 38 us, 10^6 lines 98 -> 97 us).
 const char* kSpanKernelSource = R"RX(
 typedef unsigned int rx_v4 __attribute__((ext_vector_type(4)));
 typedef long long i64;
@@ -1809,11 +1813,16 @@ extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1
             win[j] = *reinterpret_cast<const rx_v4*>(head + 16 * (B + j <= last ? B + j : 0));
     }
     i64 sid = X.offsets ? rx_lower_bound(X.offsets, X.n, o0 - skew + r0 * RX_REGION, lane) : 0;
-    i64 ahead[4];   // the first string starts of the region to come
+    // the first string starts of the region to come (without offsets: of the
+    // text's first bytes, and not used), loaded without a branch, which would
+    // make the wavefront wait for them where they are loaded
+    const i64* const starts_at = X.offsets ? X.offsets : reinterpret_cast<const i64*>(head);
+    const i64 starts_n = X.offsets ? X.n : 0;
+    i64 ahead[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const i64 i = sid + 64 * k + lane;
-        ahead[k] = X.offsets ? X.offsets[i <= X.n ? i : X.n] : 0;
+        ahead[k] = starts_at[i <= starts_n ? i : starts_n];
     }
     for (i64 r = r0; r < r1; ++r) {
         const i64 S = o0 - skew + r * RX_REGION;
@@ -1886,12 +1895,13 @@ extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1
                 pl[(4 * q + i) * 128 + 64 + lane] = (rx_v4){x[8 * i + 4], x[8 * i + 5], x[8 * i + 6], x[8 * i + 7]};
             }
         }
-        if (r + 1 < r1) {   // the next region's bytes and starts, on their way while this one runs
+        // the next region's starts and bytes, on their way while this one runs
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const i64 i = next + 64 * k + lane;
-                ahead[k] = X.offsets ? X.offsets[i <= X.n ? i : X.n] : 0;
-            }
+        for (int k = 0; k < 4; ++k) {
+            const i64 i = next + 64 * k + lane;
+            ahead[k] = starts_at[i <= starts_n ? i : starts_n];
+        }
+        if (r + 1 < r1) {
             const i64 B = (r + 1) * (RX_REGION / 16) + lane * 32;
 #pragma unroll
             for (int j = 0; j < 32; ++j)
@@ -1899,7 +1909,7 @@ extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1
         }
         rx_lds_order();
         // -- the slots --
-        u32 s[RX_NS], fin[RX_NS], acc = 0u, any = 0u;
+        u32 s[RX_NS], fin[RX_NS], acc = 0u, any = 0u;   // any: the positions with new accepts
 #pragma unroll
         for (int k = 0; k < RX_NS; ++k) s[k] = 0u;
         {
@@ -1918,7 +1928,7 @@ extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1
                 for (int k = 0; k < RX_NS; ++k) s[k] &= keep;
                 const u32 fresh = acc & ~before;
                 ri[t * 64 + lane] = fresh;
-                any |= fresh;
+                any |= (fresh ? 1u : 0u) << t;
                 m = mn;
                 lo = ln;
                 hi = hn;
@@ -1935,10 +1945,17 @@ extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1
             left |= s[k];
         }
         if (lane == 63) any = 0u;   // the next region's
+        // fixed lengths: where in which string the window begins (where its
+        // first string does, in the text's first)
+        const i64 q0 = X.offsets ? 0 : (S > 0 ? S : 0) / X.stride, in0 = X.offsets ? 0 : (S > 0 ? S : 0) - q0 * X.stride;
         // the string that holds byte t of slot 32 lane + j
         auto string_of = [&](int j, int t) -> i64 {
             const i64 at = S + (32 * lane + j) * 16 + t;
-            if (!X.offsets) return X.n == 1 ? 0 : at / X.stride;
+            if (!X.offsets) {
+                const i64 in = in0 + (S > 0 ? at - S : at);   // less than the stride and a window
+                if (X.stride >= (1 << 30)) return q0 + (in >= X.stride ? 1 : 0);
+                return q0 + (u32)in / (u32)X.stride;
+            }
             if (exact) {
                 int k = starts;
 #pragma unroll
@@ -1954,6 +1971,9 @@ extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1
             }
             return lo;
         };
+        // (a position's words are read while the one before runs)
+        u32 ml = mk[lane], mu = mk[up];
+        rx_v4 lo = pl[lane], hi = pl[64 + lane], lu = pl[up], hu = pl[64 + up];
         for (int u = 0; __ballot(left != 0u) != 0ull; ++u) {
             if ((u & 15) == 0) {
                 if (u == 31 * 16) {   // past the last lane: in table form, or not at all
@@ -1980,17 +2000,23 @@ extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1
                     if (__ballot(left != 0u) == 0ull) break;
                 }
             }
-            const int t = u & 15, q = (u >> 4) + 1;
-            const u32 keep = ~__builtin_amdgcn_alignbit(mk[t * 64 + up], mk[t * 64 + lane], q);
-            const rx_v4 lo = pl[t * 128 + lane], hi = pl[t * 128 + 64 + lane];
-            const rx_v4 lu = pl[t * 128 + up], hu = pl[t * 128 + 64 + up];
+            const int q = (u >> 4) + 1;
+            const u32 keep = ~__builtin_amdgcn_alignbit(mu, ml, q);
+            const u32 x0 = __builtin_amdgcn_alignbit(lu.x, lo.x, q), x1 = __builtin_amdgcn_alignbit(lu.y, lo.y, q),
+                      x2 = __builtin_amdgcn_alignbit(lu.z, lo.z, q), x3 = __builtin_amdgcn_alignbit(lu.w, lo.w, q),
+                      x4 = __builtin_amdgcn_alignbit(hu.x, hi.x, q), x5 = __builtin_amdgcn_alignbit(hu.y, hi.y, q),
+                      x6 = __builtin_amdgcn_alignbit(hu.z, hi.z, q), x7 = __builtin_amdgcn_alignbit(hu.w, hi.w, q);
+            const int t = (u + 1) & 15;
+            ml = mk[t * 64 + lane];
+            mu = mk[t * 64 + up];
+            lo = pl[t * 128 + lane];
+            hi = pl[t * 128 + 64 + lane];
+            lu = pl[t * 128 + up];
+            hu = pl[t * 128 + 64 + up];
             u32 b = 0u;
 #pragma unroll
             for (int k = 0; k < RX_NS; ++k) s[k] &= keep;
-            rx_step_rest(s, b, __builtin_amdgcn_alignbit(lu.x, lo.x, q), __builtin_amdgcn_alignbit(lu.y, lo.y, q),
-                         __builtin_amdgcn_alignbit(lu.z, lo.z, q), __builtin_amdgcn_alignbit(lu.w, lo.w, q),
-                         __builtin_amdgcn_alignbit(hu.x, hi.x, q), __builtin_amdgcn_alignbit(hu.y, hi.y, q),
-                         __builtin_amdgcn_alignbit(hu.z, hi.z, q), __builtin_amdgcn_alignbit(hu.w, hi.w, q));
+            rx_step_rest(s, b, x0, x1, x2, x3, x4, x5, x6, x7);
             left = 0u;
             if (__ballot(b != 0u) != 0ull) {
 #pragma unroll
@@ -2008,26 +2034,20 @@ extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1
                 late |= b;
             }
         }
-        // -- accepts --
+        // -- accepts: every lane its next one --
         while (late) {
             const int j = __builtin_ctz(late);
             late &= late - 1;
             rx_span_accept(X, string_of(j, 15), 0);
         }
-        if (__ballot(any != 0u) != 0ull) {
-            u32 fr[16];
-#pragma unroll
-            for (int t = 0; t < 16; ++t) fr[t] = any ? ri[t * 64 + lane] : 0u;
-#pragma unroll
-            for (int t = 0; t < 16; ++t) {
-                u32 f = fr[t];
-                while (f) {
-                    const int j = __builtin_ctz(f);
-                    f &= f - 1;
-                    const i64 at = S + (32 * lane + j) * 16 + t;
-                    if (at >= o0 && at < oN) rx_span_accept(X, string_of(j, t), at);
-                }
-            }
+        while (any) {
+            const int t = __builtin_ctz(any);
+            const u32 f = ri[t * 64 + lane];
+            const int j = __builtin_ctz(f);
+            if (f & (f - 1)) ri[t * 64 + lane] = f & (f - 1);
+            else any &= any - 1;
+            const i64 at = S + (32 * lane + j) * 16 + t;
+            if (at >= o0 && at < oN) rx_span_accept(X, string_of(j, t), at);
         }
         sid = next;
     }
