@@ -218,11 +218,20 @@ def _keep_for_stream(t, stream):
         t.record_stream(stream)
 
 
+_raw_stream = None   # device index -> the current stream's handle
+
+
 def _stream_handle(stream=None):
+    """The stream's handle, for a c_void_p argument (None, the null stream, for 0)."""
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream or None
     import torch
 
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if _raw_stream is None:   # the handle without a Stream object around it, where torch has that
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda d: torch.cuda.current_stream(d).cuda_stream)
+    return _raw_stream(torch.cuda.current_device()) or None
 
 
 class Program:
@@ -375,14 +384,12 @@ def match(prog: Program, data, offsets, out=None, launch=None, stream=None):
     if out is None:
         out = torch.empty(max(n, 0), dtype=torch.uint8, device=offsets.device)
     sh = _stream_handle(stream)
-    dptr = ctypes.c_void_p(data.data_ptr() if data.numel() else offsets.data_ptr())
+    dptr = data.data_ptr() if data.numel() else offsets.data_ptr()
     if launch is None:
-        _check(lib().rx_match(prog.handle, dptr, ctypes.c_void_p(offsets.data_ptr()), n,
-                              ctypes.c_void_p(out.data_ptr()), sh))
+        _check(lib().rx_match(prog._h, dptr, offsets.data_ptr(), n, out.data_ptr(), sh))
     else:
         L = launch if isinstance(launch, rx_launch) else rx_launch(*launch)
-        _check(lib().rx_match_ex(prog.handle, dptr, ctypes.c_void_p(offsets.data_ptr()), n,
-                                 ctypes.c_void_p(out.data_ptr()), ctypes.byref(L), sh))
+        _check(lib().rx_match_ex(prog._h, dptr, offsets.data_ptr(), n, out.data_ptr(), ctypes.byref(L), sh))
     return out
 
 
