@@ -518,7 +518,7 @@ int64_t rx_match_multi_workspace(int64_t n, int32_t n_progs, const rx_multi_conf
  * (the generic lockstep machine of Def. 5.3 per (program, string)).  Searched
  * programs that do not match the empty string run over equal spans of the
  * strings' bytes (as in rx_match; cfg's edges, block and grid do not concern
- * them).  For the others, strings are bucketed by length on the device; work items of up to `block`
+ * them) while programs x strings are below 7,000,000.  For the others, strings are bucketed by length on the device; work items of up to `block`
  * strings of one bucket against one program are generated on the device,
  * longest bucket first, and pulled by a persistent kernel from an atomic
  * queue.  d_out is n_progs x n bytes, row p for program p.  d_work is caller

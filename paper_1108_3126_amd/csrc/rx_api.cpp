@@ -843,7 +843,7 @@ int rx_match_multi(const rx_program* const* progs, int32_t n_progs, const uint8_
         graph_key(topo, n_progs);
         for (int i = 0; i < n_progs; ++i) {   // which kernels run, and their LDS
             graph_key(topo, m.progs[i].L);
-            graph_key(topo, m.progs[i].prefix >= 0);
+            graph_key(topo, m.progs[i].prefix >= 0 && n * n_progs < kSpanPairs);
         }
         graph_key(topo, m.n_edges);
         graph_key(topo, m.edges);

@@ -82,6 +82,7 @@ inline WorkItem span_item(int32_t prog, int64_t line0, int32_t count, int32_t B,
     return {prog | B << 8, count, line0, (int64_t)r0 | (int64_t)nr << 32};
 }
 constexpr int kSpanQueueThreads = 256;   // threads of the span kernel's workgroups in batched matching
+constexpr int64_t kSpanPairs = 7000000;  // (program, string) pairs from which batched matching runs over buckets (launch_multi)
 
 struct MultiArgs {
     ProgDesc progs[kMaxItemProgs];

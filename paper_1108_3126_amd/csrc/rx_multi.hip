@@ -930,10 +930,17 @@ int launch_multi(const MultiArgs& m) {
     // Searched programs run over equal spans of the text's bytes, the others
     // one lane per string over length buckets.  Measured: 4 programs x 20,000
     // lines 250 us over spans, 2,940 us over the buckets, where the longest
-    // line (4,096 bytes) is one serial chain.
+    // line (4,096 bytes) is one serial chain.  Buckets of many lines hide that
+    // chain, and a lane there stops at its line's accept while a span reads on:
+    // 16 programs x 100,000 lines 1.67 ms over spans, 4.88 over the buckets;
+    // 300,000 4.96 and 6.20; 450,000 7.40 and 7.21; 700,000 11.5 and 9.21;
+    // 4 * 10^6 65 and 47.  The two meet near 6.9 * 10^6 (program, line) pairs:
+    // from 7 * 10^6 on, everything runs over the buckets.
     uint8_t spans[kMaxItemProgs], plain[kMaxItemProgs];
     int n_spans = 0, n_plain = 0;
-    for (int i = 0; i < m.n_progs; ++i) (m.progs[i].prefix >= 0 ? spans[n_spans++] : plain[n_plain++]) = (uint8_t)i;
+    const bool few = m.n * m.n_progs < kSpanPairs;
+    for (int i = 0; i < m.n_progs; ++i)
+        (few && m.progs[i].prefix >= 0 ? spans[n_spans++] : plain[n_plain++]) = (uint8_t)i;
     std::stable_sort(spans, spans + n_spans, [&](uint8_t x, uint8_t y) { return m.progs[x].W > m.progs[y].W; });
     uint8_t* w = static_cast<uint8_t*>(m.work);
     auto al = [](int64_t x) { return (x + 255) & ~int64_t(255); };
