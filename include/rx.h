@@ -485,6 +485,10 @@ int rx_match_multi_prepare(const rx_program* const* progs, int32_t n_progs, cons
  * rx_program_jit_source. */
 int rx_program_jit_planes_source(const rx_program* prog, char* buf, size_t cap, size_t* len);
 
+/* The source of the circuit over equal spans of bytes (see rx_match), as
+ * rx_program_jit_source; empty where the program has no such form. */
+int rx_program_jit_spans_source(const rx_program* prog, char* buf, size_t cap, size_t* len);
+
 /* The same check on any code object (an AMDGPU ELF of len bytes, owned by the
  * caller) for the function `kernel` compiled for `arch` (e.g. "gfx950"):
  * *violations = instructions that name an accumulation register other than

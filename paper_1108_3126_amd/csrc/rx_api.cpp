@@ -948,6 +948,20 @@ int rx_program_jit_planes_source(const rx_program* prog, char* buf, size_t cap, 
     RX_GUARD_END
 }
 
+int rx_program_jit_spans_source(const rx_program* prog, char* buf, size_t cap, size_t* len) {
+    RX_GUARD_BEGIN
+    if (!prog) return fail(RX_EINVAL, "program is NULL");
+    const std::string s = jit_spans_source(*reinterpret_cast<const Program*>(prog));
+    if (len) *len = s.size();
+    if (buf && cap) {
+        const size_t k = s.size() < cap - 1 ? s.size() : cap - 1;
+        std::memcpy(buf, s.data(), k);
+        buf[k] = 0;
+    }
+    return RX_OK;
+    RX_GUARD_END
+}
+
 int rx_program_jit_stats(const rx_program* prog, int32_t* ready, int32_t* state_words, int32_t* ops) {
     if (!prog) return fail(RX_EINVAL, "program is NULL");
     int ns = 0, no = 0;

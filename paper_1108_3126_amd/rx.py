@@ -107,6 +107,7 @@ SIGNATURES = {
     "rx_program_jit_selfcheck": (ctypes.c_int, [_VP, ctypes.POINTER(_I32), ctypes.POINTER(_I32)]),
     "rx_match_multi_prepare": (ctypes.c_int, [ctypes.POINTER(_VP), _I32, ctypes.c_char_p, ctypes.POINTER(_I32)]),
     "rx_program_jit_planes_source": (ctypes.c_int, [_VP, ctypes.c_char_p, _SZ, ctypes.POINTER(_SZ)]),
+    "rx_program_jit_spans_source": (ctypes.c_int, [_VP, ctypes.c_char_p, _SZ, ctypes.POINTER(_SZ)]),
     "rx_isa_check_staging": (ctypes.c_int, [ctypes.c_char_p, _SZ, ctypes.c_char_p, ctypes.c_char_p,
                                             ctypes.POINTER(_I32)]),
     "rx_match_first": (ctypes.c_int, [_VP, _VP, _VP, _I64, _VP, _VP]),
@@ -287,6 +288,14 @@ class Program:
         _check(lib().rx_program_jit_planes_source(self._h, None, 0, ctypes.byref(n)))
         buf = ctypes.create_string_buffer(n.value + 1)
         _check(lib().rx_program_jit_planes_source(self._h, buf, n.value + 1, ctypes.byref(n)))
+        return buf.value.decode()
+
+    def jit_spans_source(self) -> str:
+        """The circuit over equal spans of bytes; empty where the program has no such form."""
+        n = ctypes.c_size_t()
+        _check(lib().rx_program_jit_spans_source(self._h, None, 0, ctypes.byref(n)))
+        buf = ctypes.create_string_buffer(n.value + 1)
+        _check(lib().rx_program_jit_spans_source(self._h, buf, n.value + 1, ctypes.byref(n)))
         return buf.value.decode()
 
     def jit_source(self) -> str:
