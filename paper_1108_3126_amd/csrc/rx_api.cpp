@@ -265,7 +265,7 @@ int rx_match_ex(const rx_program* prog, const uint8_t* d_bytes, const int64_t* d
         int64_t* slot = nullptr;
         if (int e = layout_slot(id, &slot)) return hip_fail(e, "layout slot");
         if (int e = launch_layout_check(d_offsets, n, d_bytes, slot, id, stream)) return hip_fail(e, "layout check");
-        if (int e = launch_sliced_offsets(P, d_bytes, slot, id, n, d_out, stream))
+        if (int e = launch_sliced_offsets(P, d_bytes, d_offsets, slot, id, n, d_out, stream))
             return hip_fail(e, "kernel launch (sliced)");
         a.skip = slot;
         a.skip_id = id;
@@ -388,7 +388,7 @@ int long_spans(const Program* P, const uint8_t* d_bytes, int64_t length, int32_t
     a.stride = length;
     a.out = d_out;
     a.first_pos = d_first;
-    a.undone = slot + 3;
+    a.undone = slot;
     if (int e = run_spans(P, a)) return hip_fail(e, "kernel launch (spans)");
     return RX_OK;
 }

@@ -231,10 +231,10 @@ int launch_lane(const LaunchArgs& a);
 int launch_spans_fill(const LaunchArgs& a);
 int launch_spans(const LaunchArgs& a);
 // One long string over spans, before the chunk-parallel kernels: a layout slot
-// {id, 0, 0, undone}; a thread that outlives its span by more than
-// kSpanLongLimit bytes (or a circuit's region) sets `undone` instead of being
+// that holds 2 * id; a thread that outlives its span by more than
+// kSpanLongLimit bytes (or a circuit's region) sets it to 1 instead of being
 // followed.  The chunk-parallel kernels given the gate do nothing where the
-// slot still holds the id and nothing undone; where a later call has taken the
+// slot still holds 2 * id; where a later call has taken the
 // slot, they run (same result).
 struct LongGate {
     const int64_t* slot = nullptr;
@@ -243,10 +243,10 @@ struct LongGate {
 constexpr int64_t kSpanLongLimit = 4096;
 int launch_span_long_begin(const LongGate& gate, uint8_t* out, int64_t* first, void* stream);
 // Equal-length consecutive strings for rx_match (rx_kernels.hip): the slot of
-// call `id` in a static per-device array of kLayoutSlots slots of four int64
-// {id, length, first offset, flaw}; launch_layout_check fills it on `stream`
-// (flaw 0: string i is bytes[first + i * length, + length), length a multiple
-// of 16 up to kLayoutMaxLength and the first byte 16-byte aligned).
+// call `id` in a static per-device array of kLayoutSlots words;
+// launch_layout_check fills it on `stream` (2 * id: string i is
+// bytes[offsets[0] + i * length, + length), length a multiple of 16 up to
+// kLayoutMaxLength and the first byte 16-byte aligned; 2 * id + 1: it is not).
 constexpr int64_t kLayoutSlots = 4096;
 constexpr int64_t kLayoutMaxLength = (int64_t)1 << 26;
 constexpr int64_t kLayoutMinStrings = 16384;   // fewer strings: the table form alone
@@ -288,8 +288,8 @@ bool jit_ready(const Program* P, int* n_state, int* n_ops);
 // rx_match's equal-length strings through the skewed kernel (the layout slot
 // of call id decides whether it runs)
 bool jit_offsets_ready(const Program* P);
-int launch_sliced_offsets(const Program* P, const uint8_t* bytes, const int64_t* slot, int64_t id, int64_t n,
-                          uint8_t* out, void* stream);
+int launch_sliced_offsets(const Program* P, const uint8_t* bytes, const int64_t* offsets, const int64_t* slot, int64_t id,
+                          int64_t n, uint8_t* out, void* stream);
 // staged[u] for staging modes u = 0..5 (see rx_program_jit_staging).
 void jit_staging(const Program* P, int32_t staged[7]);
 // Plane-form circuits (rx_jit.cpp): one module per list of programs.

@@ -784,8 +784,8 @@ extern "C" __global__ __launch_bounds__(64) void rx_long_chunks(const unsigned c
                                                                 long long length, long long Lc,
                                                                 u32* __restrict__ seg_maps,
                                                                 u32* __restrict__ chunk_maps,
-                                                                const long long* __restrict__ gate, long long id) {
-    if (gate && gate[0] == id && gate[3] == 0) return;   // the span form has the result
+                                                                const long long* gate, long long id) {
+    if (gate && *gate == 2 * id) return;   // the span form has the result
     const long long g = blockIdx.x;
     const int lane = threadIdx.x;
     const long long base = g * 2048 * Lc;
@@ -831,8 +831,8 @@ extern "C" __global__ __launch_bounds__(64) void rx_long_chunks(const unsigned c
 // consecutive segments, then the lanes in order), applied to the start state.
 extern "C" __global__ __launch_bounds__(64) void rx_long_compose(const u32* __restrict__ seg_maps, long long G,
                                                                  unsigned char* __restrict__ out,
-                                                                 const long long* __restrict__ gate, long long id) {
-    if (gate && gate[0] == id && gate[3] == 0) return;
+                                                                 const long long* gate, long long id) {
+    if (gate && *gate == 2 * id) return;
     const int lane = threadIdx.x;
     const long long per = (G + 63) / 64, g0 = lane * per, g1 = g0 + per < G ? g0 + per : G;
     u32 f[RX_M];
@@ -1355,22 +1355,24 @@ extern "C" __global__ __launch_bounds__(128, 1) void rx_sliced_fixed_skew_w(cons
     rx_skew<false, false>(bytes, length, n, out, nullptr, rx_tile);
 }
 
-// rx_match's equal-length strings: the layout slot of call `id` (see the
-// layout check: {id, length, first offset, flaw}) holds the length and the
-// first string's offset; the kernel does nothing unless the slot is this
-// call's and has no flaw (the table form then matches the strings).
+// rx_match's equal-length strings: the kernel does nothing unless the layout
+// slot holds 2 * id, this call's id and no flaw (see the layout check; the
+// table form then matches the strings).  Length and first string come from the
+// call's own offsets.
 extern "C" __global__ __launch_bounds__(128, 1) void rx_sliced_offsets_skew(const unsigned char* __restrict__ bytes,
-        const long long* __restrict__ slot, long long id, long long n, unsigned char* __restrict__ out) {
+        const long long* __restrict__ offsets, const long long* slot, long long id, long long n,
+        unsigned char* __restrict__ out) {
     extern __shared__ u32 rx_tile[];
-    if (slot[0] != id || slot[3] != 0) return;
-    rx_skew<true, false>(bytes + slot[2], slot[1], n, out, nullptr, rx_tile);
+    if (__hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 2 * id) return;
+    rx_skew<true, false>(bytes + offsets[0], offsets[1] - offsets[0], n, out, nullptr, rx_tile);
 }
 
 extern "C" __global__ __launch_bounds__(128, 1) void rx_sliced_offsets_skew_w(const unsigned char* __restrict__ bytes,
-        const long long* __restrict__ slot, long long id, long long n, unsigned char* __restrict__ out) {
+        const long long* __restrict__ offsets, const long long* slot, long long id, long long n,
+        unsigned char* __restrict__ out) {
     extern __shared__ u32 rx_tile[];
-    if (slot[0] != id || slot[3] != 0) return;
-    rx_skew<false, false>(bytes + slot[2], slot[1], n, out, nullptr, rx_tile);
+    if (__hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 2 * id) return;
+    rx_skew<false, false>(bytes + offsets[0], offsets[1] - offsets[0], n, out, nullptr, rx_tile);
 }
 
 // Earliest accepting prefix of every string (the root is not nullable:
@@ -1705,7 +1707,7 @@ struct rx_span_text {
     i64* first;           // -1 before the launch (earliest accepts wanted)
     const u32 *first_row, *follow, *bytemask;   // the program's tables (threads that outlive the last lane)
     int prefix;
-    const i64* skip;      // rx_match's layout slot: nothing to do when it holds skip_id and no flaw
+    const i64* skip;      // rx_match's layout slot: nothing to do when it holds 2 * skip_id
     i64 skip_id;
     i64* undone;          // not NULL: set, instead of following a thread past the last lane
 };
@@ -1793,7 +1795,7 @@ extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1
     u32* bm = rx_sp;                               // one bit per byte, before the planes are in place
     const int lane = threadIdx.x;
     const int up = lane < 63 ? lane + 1 : 63;
-    if (X.skip && X.skip[0] == X.skip_id && X.skip[3] == 0) return;
+    if (X.skip && __hip_atomic_load(X.skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 2 * X.skip_id) return;
     const i64 o0 = X.offsets ? X.offsets[0] : 0, oN = X.offsets ? X.offsets[X.n] : X.n * X.stride;
     if (oN <= o0) return;
     const int skew = (int)((unsigned long long)(X.bytes + o0) & 15ull);
@@ -2465,7 +2467,8 @@ int jit_selfcheck(const Program& P, JitKernel* K, hipFunction_t* const* staged, 
     if (e == hipSuccess) e = hipMalloc(&d_out, (size_t)n);
     if (e == hipSuccess) e = hipMalloc(&d_first, 8 * (size_t)n);
     if (e == hipSuccess) e = hipMalloc(&d_slot, 4 * sizeof(int64_t));
-    const int64_t slot[4] = {1, length, 0, 0};   // an equal-length batch, as the layout check would find it
+    // a layout slot that says equal lengths, the first two offsets, a word for what the span form leaves undone
+    const int64_t slot[4] = {2, 0, length, 0};
     if (e == hipSuccess) e = hipMemcpy(d_bytes, B.bytes.data(), (size_t)(n * length), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(d_slot, slot, sizeof(slot), hipMemcpyHostToDevice);
     std::vector<uint8_t> out((size_t)n);
@@ -2478,9 +2481,10 @@ int jit_selfcheck(const Program& P, JitKernel* K, hipFunction_t* const* staged, 
         void* o = d_out;
         void* fo = d_first;
         const void* sl = d_slot;
+        const void* of = d_slot + 1;
         void* a0[] = {&b, &len, &nn, &o};
         void* a1[] = {&b, &len, &nn, &fo};
-        void* a2[] = {&b, &sl, &id, &nn, &o};
+        void* a2[] = {&b, &of, &sl, &id, &nn, &o};
         hipError_t r = hipMemsetAsync(kind == 1 ? (void*)d_first : (void*)d_out, 0xff,
                                       kind == 1 ? 8 * (size_t)n : (size_t)n, st);
         if (r == hipSuccess)
@@ -2758,17 +2762,18 @@ bool jit_offsets_ready(const Program* P) {
     return K && K->skew_offsets;
 }
 
-int launch_sliced_offsets(const Program* P, const uint8_t* bytes, const int64_t* slot, int64_t id, int64_t n,
-                          uint8_t* out, void* stream) {
+int launch_sliced_offsets(const Program* P, const uint8_t* bytes, const int64_t* offsets, const int64_t* slot, int64_t id,
+                          int64_t n, uint8_t* out, void* stream) {
     const JitKernel* K = static_cast<const JitKernel*>(P->jit);
     if (!K || !K->skew_offsets) return (int)hipErrorInvalidValue;
     const long long grid = (n + 2047) / 2048;
     const unsigned lds = 2048 * 32 + 2 * 2048 * 4;
     long long i = id, nn = n;
     const void* b = bytes;
+    const void* of = offsets;
     const void* sl = slot;
     void* o = out;
-    void* args[] = {&b, &sl, &i, &nn, &o};
+    void* args[] = {&b, &of, &sl, &i, &nn, &o};
     return (int)hipModuleLaunchKernel(K->skew_offsets, (unsigned)grid, 1, 1, 128, 1, 1, lds, (hipStream_t)stream,
                                       args, nullptr);
 }

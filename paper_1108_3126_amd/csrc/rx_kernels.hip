@@ -50,7 +50,7 @@ struct KArgs {
     int64_t rows_len, rows_cl;
     int32_t rows_per_chunk, rows_pad;
     // rx_match's layout slot: the kernel does nothing when the slot holds
-    // skip_id and no flaw (the bit-sliced kernel has matched the strings)
+    // 2 * skip_id (the bit-sliced kernel has matched the strings)
     const int64_t* skip;
     int64_t skip_id;
 };
@@ -58,7 +58,7 @@ struct KArgs {
 // true when the layout check of this call found equal lengths and the
 // bit-sliced kernel took the strings
 __device__ __forceinline__ bool taken_by_sliced(const KArgs& a) {
-    return a.skip && a.skip[0] == a.skip_id && a.skip[3] == 0;
+    return a.skip && __hip_atomic_load(a.skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 2 * a.skip_id;
 }
 
 // Start and byte range of row j of the chunk-parallel run.
@@ -597,7 +597,7 @@ int launch_wave(const LaunchArgs& a) {
 }
 
 // the span form has the long string's result
-__device__ __forceinline__ bool long_done(const LongGate& g) { return g.slot && g.slot[0] == g.id && g.slot[3] == 0; }
+__device__ __forceinline__ bool long_done(const LongGate& g) { return g.slot && *g.slot == 2 * g.id; }
 
 // Chunk-parallel matching, second pass: apply the chunks' relations in order.
 // S starts as row 0 (chunk 0 run from First); for chunk c the new set is the
@@ -825,12 +825,14 @@ int long_scratch(void** ptr) {
 // Layout check of rx_match's strings, so that equal-length consecutive
 // strings can go to the bit-sliced kernel without the host reading the
 // offsets.  Each call takes the slot of its id (id modulo the slot count) in
-// a static array per device: {id, length, first offset, flaw}.  The readers
-// of a slot act only while it holds their id, so a later call that takes the
-// same slot sends the earlier call's strings to the table form, which gives
-// the same bits; ids only grow, so once a reader has seen another id every
-// later reader of that call sees one too.
-static __device__ __align__(256) int64_t layout_slots[kLayoutSlots * 4];
+// a static array per device: one word, 2 * id, plus 1 where the check finds a
+// flaw.  The readers of a slot act only while it holds their id, so a later
+// call that takes the same slot sends the earlier call's strings to the table
+// form, which gives the same bits; ids only grow, so once a reader has seen
+// another id every later reader of that call sees one too.  (A captured call
+// keeps its id, and meets live calls' on its slot for ever: id and finding are
+// one word so that no reader can take one from one call and one from another.)
+static __device__ __align__(256) int64_t layout_slots[kLayoutSlots];
 
 namespace {
 __global__ void k_layout_begin(const int64_t* __restrict__ offsets, int64_t n, const uint8_t* bytes, int64_t* slot,
@@ -838,21 +840,18 @@ __global__ void k_layout_begin(const int64_t* __restrict__ offsets, int64_t n, c
     const int64_t o0 = offsets[0], len = offsets[1] - o0;
     const bool ok = len > 0 && (len & 15) == 0 && len <= kLayoutMaxLength && offsets[n] - o0 == n * len &&
                     (reinterpret_cast<uintptr_t>(bytes + o0) & 15) == 0;
-    slot[1] = len;
-    slot[2] = o0;
-    slot[3] = ok ? 0 : 1;
-    slot[0] = id;
+    __hip_atomic_store(slot, 2 * id + (ok ? 0 : 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __global__ __launch_bounds__(256) void k_layout_check(const int64_t* __restrict__ offsets, int64_t n,
                                                       int64_t* slot, int64_t id) {
-    if (slot[0] != id || slot[3] != 0) return;
-    const int64_t len = slot[1], o0 = slot[2];
+    if (__hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 2 * id) return;
+    const int64_t o0 = offsets[0], len = offsets[1] - o0;
     bool flaw = false;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= n; i += (int64_t)gridDim.x * blockDim.x)
         flaw |= offsets[i] != o0 + i * len;
     if (__any(flaw) && (threadIdx.x & 63) == 0)
-        atomicOr(reinterpret_cast<unsigned long long*>(slot + 3), 1ull);
+        atomicCAS(reinterpret_cast<unsigned long long*>(slot), (unsigned long long)(2 * id), (unsigned long long)(2 * id + 1));
 }
 }  // namespace
 
@@ -869,7 +868,7 @@ int layout_slot(int64_t id, int64_t** slot) {
         if (!p) return (int)hipErrorInvalidSymbol;
         it = by_device.emplace(dev, static_cast<int64_t*>(p)).first;
     }
-    *slot = it->second + (id % kLayoutSlots) * 4;
+    *slot = it->second + id % kLayoutSlots;
     return 0;
 }
 

@@ -30,7 +30,7 @@ template <int W, int T, bool FIRST>
 __global__ __launch_bounds__(T) void k_spans(SpanArgs a) {
     extern __shared__ __align__(16) uint32_t lds[];
     constexpr int WP = span_row_words(W);
-    if (a.skip && a.skip[0] == a.skip_id && a.skip[3] == 0) return;
+    if (a.skip && __hip_atomic_load(a.skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 2 * a.skip_id) return;
     const int64_t o0 = a.text.offsets ? a.text.offsets[0] : 0;
     const int64_t oN = a.text.offsets ? a.text.offsets[a.text.n] : a.text.n * a.text.stride;
     const int64_t total = oN - o0 + 15;
@@ -77,8 +77,7 @@ int launch_spans_fill(const LaunchArgs& a) {
 
 namespace {
 __global__ void k_span_long_begin(int64_t* slot, int64_t id, uint8_t* out, int64_t* first) {
-    slot[1] = slot[2] = slot[3] = 0;
-    slot[0] = id;
+    __hip_atomic_store(slot, 2 * id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (first) *first = -1;
     else *out = 0;
 }

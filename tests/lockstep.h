@@ -133,6 +133,9 @@ static inline T atomicMin(T* p, T v) {
     if (v < o) *p = v;
     return o;
 }
+#define __HIP_MEMORY_SCOPE_AGENT 0
+#define __hip_atomic_load(p, order, scope) (*(p))
+#define __hip_atomic_store(p, v, order, scope) (void)(*(p) = (v))
 #define __builtin_amdgcn_wave_barrier() (void)lockstep::wait(lockstep::kWave, 0)
 static inline uint32_t lockstep_alignbit(uint32_t hi, uint32_t lo, uint32_t s) {
     return (uint32_t)((((uint64_t)hi << 32) | lo) >> (s & 31));
