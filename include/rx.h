@@ -310,7 +310,9 @@ int rx_match_first_fixed(const rx_program* prog, const uint8_t* d_bytes, int64_t
  * run first, as in rx_match; only if a thread outlives its span by more than
  * 4,096 bytes (or the circuit's region), which the device finds, do the kernels
  * above run too (they are queued either way, and return at once; the
- * device's finding is kept in a slot as for rx_match).
+ * device's finding is kept in the workspace, behind what they use, and where
+ * the default count of chunks leaves no room for it there is one chunk fewer; a
+ * workspace that still has none runs them alone).
  * rx_match_long_workspace(.., chunks = 0, ..) covers all forms.
  * Errors: RX_EINVAL (NULL buffers, negative sizes, short workspace),
  * RX_ENOTUPLOADED, RX_ETOOBIG (sets above 128 words), RX_EHIP. */

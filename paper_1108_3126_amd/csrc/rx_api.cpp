@@ -325,6 +325,16 @@ size_t long_sets_bytes(const Program* P, int64_t C) {
     return ((size_t)long_rows(P, C) * (size_t)P->W * 4 + 7) & ~(size_t)7;
 }
 size_t long_rows_bytes(const Program* P, int64_t C) { return long_sets_bytes(P, C) + 8 * (size_t)long_rows(P, C); }
+
+// A string that runs over spans before the chunks (see long_spans).
+bool long_spans_apply(const Program* P, int64_t length, int32_t chunks) {
+    return P->span_prefix >= 0 && chunks == 0 && length >= 4096;
+}
+// Its default chunks are one fewer, so that the workspace has room for the
+// spans' gate behind the rows: a chunk's rows are at least four of twelve bytes.
+void long_chunks_beside_spans(const Program* P, int64_t length, int32_t chunks, int64_t* C, int64_t* cl) {
+    if (long_spans_apply(P, length, chunks) && *C > 1) long_chunks(P, length, (int32_t)(*C - 1), C, cl);
+}
 }  // namespace
 
 int rx_match_long_workspace(const rx_program* prog, int64_t length, int32_t chunks, size_t* bytes) {
@@ -337,7 +347,10 @@ int rx_match_long_workspace(const rx_program* prog, int64_t length, int32_t chun
     *bytes = long_rows_bytes(P, C);
     // rx_match_long's circuit form (chunks = 0 with a compiled circuit) needs its segment maps
     const int64_t circuit = chunks == 0 ? long_chunk_work_bytes(P, length) : -1;
-    if (circuit > 0 && (size_t)circuit > *bytes) *bytes = (size_t)circuit;
+    if (circuit > 0) {
+        const size_t c = (size_t)circuit + (long_spans_apply(P, length, chunks) ? kLongGateBytes : 0);
+        if (c > *bytes) *bytes = c;
+    }
     return RX_OK;
     RX_GUARD_END
 }
@@ -369,17 +382,17 @@ int match_long_run(const Program* P, const uint8_t* d_bytes, int64_t length, int
     return RX_OK;
 }
 
-// One long string over spans, with a layout slot for what is undone; gate->slot
-// stays NULL where that does not apply (no such program, a short string, a chunk
-// count that the caller chose).  Measured, a 17-word circuit, text without a
-// match: 8 MiB 19 us (147 us as circuit chunks, each run from every word
-// alone).
-int long_spans(const Program* P, const uint8_t* d_bytes, int64_t length, int32_t chunks, uint8_t* d_out,
-               int64_t* d_first, LongGate* gate, void* stream) {
-    if (P->span_prefix < 0 || chunks != 0 || length < 4096) return RX_OK;
-    gate->id = next_slot_id();
-    int64_t* slot = nullptr;
-    if (int e = layout_slot(gate->id, &slot)) return hip_fail(e, "layout slot");
+// One long string over spans, with the gate (see LongGate) in the workspace's
+// bytes from `used` on; gate->slot stays NULL where spans do not apply (no such
+// program, a short string, a chunk count that the caller chose) or the
+// workspace has no room for the gate.  Measured, a 17-word circuit, text
+// without a match: 8 MiB 19 us (147 us as circuit chunks, each run from every
+// word alone).
+int long_spans(const Program* P, const uint8_t* d_bytes, int64_t length, int32_t chunks, void* d_work, size_t used,
+               size_t work_bytes, uint8_t* d_out, int64_t* d_first, LongGate* gate, void* stream) {
+    if (!long_spans_apply(P, length, chunks) || work_bytes < used + kLongGateBytes) return RX_OK;
+    int64_t* slot = reinterpret_cast<int64_t*>((reinterpret_cast<uintptr_t>(d_work) + used + 7) & ~uintptr_t(7));
+    gate->id = 1;
     gate->slot = slot;
     if (int e = launch_span_long_begin(*gate, d_out, d_first, stream)) return hip_fail(e, "kernel launch (spans)");
     LaunchArgs a;
@@ -415,7 +428,9 @@ int rx_match_long(const rx_program* prog, const uint8_t* d_bytes, int64_t length
     const int64_t circuit_need = chunks == 0 && length <= (int64_t(1) << 40) ? long_chunk_work_bytes(P, length) : -1;
     LongGate gate;
     if (circuit_need >= 0 && (size_t)circuit_need <= work_bytes) {
-        if (int rc = long_spans(P, d_bytes, length, chunks, d_out, nullptr, &gate, stream)) return rc;
+        if (int rc = long_spans(P, d_bytes, length, chunks, d_work, (size_t)circuit_need, work_bytes, d_out, nullptr, &gate,
+                                stream))
+            return rc;
         if (int e = launch_long_chunks(P, d_bytes, length, d_work, d_out, gate, stream)) return hip_fail(e, "kernel launch");
         return RX_OK;
     }
@@ -425,7 +440,9 @@ int rx_match_long(const rx_program* prog, const uint8_t* d_bytes, int64_t length
     if (work_bytes < need)
         return fail(RX_EINVAL, "workspace holds " + std::to_string(work_bytes) + " bytes; this run needs " +
                                    std::to_string(need) + " (rx_match_long_workspace)");
-    if (int rc = long_spans(P, d_bytes, length, chunks, d_out, nullptr, &gate, stream)) return rc;
+    long_chunks_beside_spans(P, length, chunks, &C, &cl);
+    if (int rc = long_spans(P, d_bytes, length, chunks, d_work, long_rows_bytes(P, C), work_bytes, d_out, nullptr, &gate, stream))
+        return rc;
     return match_long_run(P, d_bytes, length, C, cl, d_work, d_out, gate, stream);
     RX_GUARD_END
 }
@@ -451,7 +468,9 @@ int rx_match_long_noalloc(const rx_program* prog, const uint8_t* d_bytes, int64_
     void* work = nullptr;
     if (int e = long_scratch(&work)) return hip_fail(e, "device address of the static workspace");
     LongGate gate;
-    if (int rc = long_spans(P, d_bytes, length, chunks, d_out, nullptr, &gate, stream)) return rc;
+    if (int rc = long_spans(P, d_bytes, length, chunks, work, kLongScratchBytes, kLongScratchBytes + kLongGateBytes, d_out,
+                            nullptr, &gate, stream))
+        return rc;
     return match_long_run(P, d_bytes, length, C, cl, work, d_out, gate, stream);
     RX_GUARD_END
 }
@@ -479,7 +498,9 @@ int rx_match_first_long(const rx_program* prog, const uint8_t* d_bytes, int64_t 
         return RX_OK;
     }
     LongGate gate;
-    if (int rc = long_spans(P, d_bytes, length, chunks, nullptr, d_first, &gate, stream)) return rc;
+    long_chunks_beside_spans(P, length, chunks, &C, &cl);
+    if (int rc = long_spans(P, d_bytes, length, chunks, d_work, long_rows_bytes(P, C), work_bytes, nullptr, d_first, &gate, stream))
+        return rc;
     LaunchArgs a;
     if (int rc = make_launch_args(P, d_bytes ? d_bytes : static_cast<const uint8_t*>(d_work),
                                   static_cast<const int64_t*>(d_work), long_rows(P, C),

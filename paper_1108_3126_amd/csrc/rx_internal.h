@@ -230,17 +230,20 @@ int launch_lane(const LaunchArgs& a);
 // those of the strings that match.
 int launch_spans_fill(const LaunchArgs& a);
 int launch_spans(const LaunchArgs& a);
-// One long string over spans, before the chunk-parallel kernels: a layout slot
-// that holds 2 * id; a thread that outlives its span by more than
-// kSpanLongLimit bytes (or a circuit's region) sets it to 1 instead of being
-// followed.  The chunk-parallel kernels given the gate do nothing where the
-// slot still holds 2 * id; where a later call has taken the
-// slot, they run (same result).
+// One long string over spans, before the chunk-parallel kernels: a word in
+// memory that belongs to the call (its workspace), 2 * id; a thread that
+// outlives its span by more than kSpanLongLimit bytes (or a circuit's region)
+// sets it to 1 instead of being followed.  The chunk-parallel kernels given the
+// gate do nothing where it holds 2 * id still.  They are two, and a second that
+// ran after a first that did not would compose what nobody wrote: so no other
+// call may write this word, and a slot of the array that rx_match's calls share
+// will not do.
 struct LongGate {
     const int64_t* slot = nullptr;
     int64_t id = 0;
 };
 constexpr int64_t kSpanLongLimit = 4096;
+constexpr size_t kLongGateBytes = 16;   // a word at an 8-byte boundary
 int launch_span_long_begin(const LongGate& gate, uint8_t* out, int64_t* first, void* stream);
 // Equal-length consecutive strings for rx_match (rx_kernels.hip): the slot of
 // call `id` in a static per-device array of kLayoutSlots words;

@@ -803,7 +803,7 @@ const char* hip_error_string(int err) { return hipGetErrorString((hipError_t)err
 // once per device with that device current, and only that address reaches a
 // kernel.  Every call on a GPU shares the GPU's copy: calls that overlap on
 // one GPU race.
-static __device__ __align__(256) unsigned char scratch[kLongScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kLongScratchBytes + kLongGateBytes];   // the rows, the spans' gate
 
 int long_scratch(void** ptr) {
     static std::mutex mu;
