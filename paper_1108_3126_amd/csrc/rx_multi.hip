@@ -177,8 +177,13 @@ __device__ __forceinline__ void span_run(const ProgDesc& P, const SpanText& X, u
 }
 
 // Persistent: a workgroup's next item is often of the program whose tables it
-// holds.
-__global__ __launch_bounds__(kSpanQueueThreads) void k_span_queue(SpanQueueArgs a) {
+// holds.  kWords: the widest sets of the list.  Up to four words leave registers
+// for four wavefronts per SIMD, as many as their LDS lets in; sixteen take
+// enough for two, whatever the sets that run (16 one-word programs, 200,000
+// lines of 100 bytes: 460 us so, 340 as four-word ones).
+constexpr int kQueueNarrow = 4;
+template <int kWords>
+__global__ __launch_bounds__(kSpanQueueThreads, kWords <= kQueueNarrow ? 4 : 2) void k_span_queue(SpanQueueArgs a) {
     extern __shared__ __align__(16) uint32_t lds[];
     __shared__ int s_item;
     const int64_t T = kSpanQueueThreads;
@@ -229,8 +234,10 @@ __global__ __launch_bounds__(kSpanQueueThreads) void k_span_queue(SpanQueueArgs 
         const bool staged = p == loaded;
         loaded = p;
         switch (P.W) {
-#define RX_SR(w) \
-    case w: span_run<w>(P, X, out, o0, oN, B, r0, r1, staged, lds); break;
+#define RX_SR(w)                                                                             \
+    case w:                                                                                  \
+        if constexpr (w <= kWords) span_run<w>(P, X, out, o0, oN, B, r0, r1, staged, lds);   \
+        break;
             RX_SR(1) RX_SR(2) RX_SR(3) RX_SR(4) RX_SR(5) RX_SR(6) RX_SR(7) RX_SR(8)
             RX_SR(9) RX_SR(10) RX_SR(11) RX_SR(12) RX_SR(13) RX_SR(14) RX_SR(15) RX_SR(16)
 #undef RX_SR
@@ -252,23 +259,29 @@ dim3 span_clear_grid(int64_t n, int rows) {
     return dim3((unsigned)(b < 1 ? 1 : b < 1024 ? b : 1024), (unsigned)rows);
 }
 
-// Dynamic LDS of the queue kernel for a list of programs, and the workgroups
+// The queue kernel for a list of programs, its dynamic LDS and the workgroups
 // that are resident with it.
-int span_queue_lds(const ProgDesc* progs, int n, int* lds, int* grid) {
+struct SpanQueueShape {
+    const void* kernel = nullptr;
+    int lds = 0, grid = 1;
+};
+
+// (of at least `widest` words)
+int span_queue_shape(const ProgDesc* progs, int n, int widest, SpanQueueShape* s) {
     int words = 0;
     for (int i = 0; i < n; ++i)
         if (progs[i].prefix >= 0) {
             const int w = span_lds_words(progs[i].W, progs[i].L, kSpanQueueThreads);
             if (w > words) words = w;
+            if (progs[i].W > widest) widest = progs[i].W;
         }
-    *lds = 4 * words;
+    s->kernel = widest <= kQueueNarrow ? (const void*)k_span_queue<kQueueNarrow> : (const void*)k_span_queue<kLaneMaxWords>;
+    s->lds = 4 * words;
     int cus = 0;
     if (hip_cu_count(&cus) || cus <= 0) cus = 256;
-    int per = (160 * 1024) / (*lds + 512);
-    *grid = cus * (per < 1 ? 1 : per > 8 ? 8 : per);
-    return *lds > 64 * 1024
-               ? (int)hipFuncSetAttribute((const void*)k_span_queue, hipFuncAttributeMaxDynamicSharedMemorySize, *lds)
-               : 0;
+    int per = (160 * 1024) / (s->lds + 512);
+    s->grid = cus * (per < 1 ? 1 : per > 8 ? 8 : per);
+    return s->lds > 64 * 1024 ? (int)hipFuncSetAttribute(s->kernel, hipFuncAttributeMaxDynamicSharedMemorySize, s->lds) : 0;
 }
 
 // -- bucketing -------------------------------------------------------------
@@ -975,11 +988,13 @@ int launch_multi(const MultiArgs& m) {
         q.head = b.head + 1;   // after the buckets' own counters
         q.n_rows = n_spans;
         for (int i = 0; i < n_spans; ++i) q.rows[i] = spans[i];
-        int lds = 0, grid = 0;
-        if (int e = span_queue_lds(m.progs, m.n_progs, &lds, &grid)) return e;
+        SpanQueueShape shape;
+        if (int e = span_queue_shape(m.progs, m.n_progs, 1, &shape)) return e;
         hipLaunchKernelGGL(k_span_clear, span_clear_grid(m.n, n_spans), dim3(256), 0, st, q, m.n);
-        hipLaunchKernelGGL(k_span_queue, dim3((unsigned)grid), dim3(kSpanQueueThreads), (size_t)lds, st, q);
-        if (hipError_t e = hipGetLastError()) return (int)e;
+        void* params[] = {&q};
+        if (hipError_t e = hipLaunchKernel(shape.kernel, dim3((unsigned)shape.grid), dim3(kSpanQueueThreads), params,
+                                           (size_t)shape.lds, st))
+            return (int)e;
     }
     if (!n_plain) return 0;
     const int gs = (int)((m.n + 255) / 256 < 1024 ? (m.n + 255) / 256 : 1024);
@@ -1032,7 +1047,7 @@ ItemKArgs item_kargs(const ItemsArgs& m) {
 // shape (one workgroup where the step has none).
 struct StepSpans {
     SpanQueueArgs args;
-    int lds = 0, grid = 1;
+    SpanQueueShape shape;
 };
 
 int step_spans(const ItemsArgs& m, StepSpans* s) {
@@ -1045,8 +1060,9 @@ int step_spans(const ItemsArgs& m, StepSpans* s) {
     s->args.n_items = m.n_span_items;
     s->args.head = m.span_head;
     s->args.n_rows = 0;
-    if (int e = span_queue_lds(m.progs, m.n_progs, &s->lds, &s->grid)) return e;
-    if (m.max_span_items < s->grid) s->grid = m.max_span_items < 1 ? 1 : m.max_span_items;
+    // one kernel for every step: a graph's node keeps its function
+    if (int e = span_queue_shape(m.progs, m.n_progs, kLaneMaxWords, &s->shape)) return e;
+    if (m.max_span_items < s->shape.grid) s->shape.grid = m.max_span_items < 1 ? 1 : m.max_span_items;
     return 0;
 }
 
@@ -1063,7 +1079,10 @@ int step_launch_direct(const StepDesc& d, void* stream) {
     StepSpans sp;
     if (int e = step_spans(d.items, &sp)) return e;
     hipLaunchKernelGGL(k_span_clear, span_clear_grid(d.items.n_lines, 1), dim3(256), 0, st, sp.args, d.items.n_lines);
-    hipLaunchKernelGGL(k_span_queue, dim3((unsigned)sp.grid), dim3(kSpanQueueThreads), (size_t)sp.lds, st, sp.args);
+    void* span_params[] = {&sp.args};
+    if (hipError_t e = hipLaunchKernel(sp.shape.kernel, dim3((unsigned)sp.shape.grid), dim3(kSpanQueueThreads), span_params,
+                                       (size_t)sp.shape.lds, st))
+        return (int)e;
     ItemKArgs k = item_kargs(d.items);
     hipLaunchKernelGGL(k_items, dim3(d.items.grid), dim3(d.items.block), kStepLds, st, k);
     if (hipError_t e = hipGetLastError()) return (int)e;
@@ -1110,8 +1129,8 @@ int step_graph_launch(StepGraph** pg, const StepDesc& d, void* stream) {
     void* span_params[] = {&g->sp.args};
     void* item_params[] = {&g->args};
     hipKernelNodeParams kc = node_params((const void*)k_span_clear, span_clear_grid(g->n_lines, 1), dim3(256), 0, clear_params);
-    hipKernelNodeParams ks = node_params((const void*)k_span_queue, dim3((unsigned)g->sp.grid), dim3(kSpanQueueThreads),
-                                         (unsigned)g->sp.lds, span_params);
+    hipKernelNodeParams ks = node_params(g->sp.shape.kernel, dim3((unsigned)g->sp.shape.grid), dim3(kSpanQueueThreads),
+                                         (unsigned)g->sp.shape.lds, span_params);
     hipKernelNodeParams ki = node_params((const void*)k_items, dim3(d.items.grid), dim3(d.items.block), kStepLds, item_params);
     if (fresh) {
         hipError_t e = hipGraphCreate(&g->graph, 0);
