@@ -409,8 +409,8 @@ int rx_match_fixed_ex(const rx_program* prog, const uint8_t* d_bytes, int64_t le
  * RX_ETOOBIG (they would not fit in registers); the table-form kernels run
  * them.  When the code object is loaded, every kernel kept is run once on a
  * seeded batch and checked against the table step (rx_program_jit_selfcheck):
- * the call then allocates about 1.1 MB of device memory for that batch, frees
- * it, and waits for the check to finish (synchronous; not for capture).
+ * the call then allocates about 1.1 MB of device memory for that batch (and, for
+ * a program with a circuit over spans, its tables' size), frees it, and waits for the check to finish (synchronous; not for capture).
  * Errors: RX_EJIT (message holds the compiler log, or the LDS-staged kernel
  * disagreed with the table step), RX_ETOOBIG, RX_EHIP.
  */
@@ -464,7 +464,8 @@ int rx_program_jit_guard(const rx_program* prog, int32_t* ran, int32_t violation
  * ran (0 before rx_program_jit or when the circuit was only compiled);
  * *dropped has bit k set when staged kernel k (the order of
  * rx_program_jit_guard) gave other bits and was dropped (the staging report
- * shows what runs instead).  The LDS-staged kernel is checked too; if it
+ * shows what runs instead), and bit 8 when the circuit over spans did (the
+ * table-form spans run instead).  The LDS-staged kernel is checked too; if it
  * disagrees, rx_program_jit fails with RX_EJIT.  Errors: RX_EINVAL (NULL
  * arguments). */
 int rx_program_jit_selfcheck(const rx_program* prog, int32_t* ran, int32_t* dropped);

@@ -2452,6 +2452,7 @@ struct SpanTextArg {
     int64_t* undone = nullptr;
 };
 constexpr unsigned kSpanLds = 4 * (16 * 8 * 64 + 2 * 16 * 64);
+constexpr int kSpanCheckBit = 8;   // of rx_program_jit_selfcheck's report
 
 int jit_selfcheck(const Program& P, JitKernel* K, hipFunction_t* const* staged, int n_staged,
                   hipFunction_t* offsets_twin, hipFunction_t* offsets_twin_w) {
@@ -2467,8 +2468,7 @@ int jit_selfcheck(const Program& P, JitKernel* K, hipFunction_t* const* staged, 
     if (e == hipSuccess) e = hipMalloc(&d_out, (size_t)n);
     if (e == hipSuccess) e = hipMalloc(&d_first, 8 * (size_t)n);
     if (e == hipSuccess) e = hipMalloc(&d_slot, 4 * sizeof(int64_t));
-    // a layout slot that says equal lengths, the first two offsets, a word for what the span form leaves undone
-    const int64_t slot[4] = {2, 0, length, 0};
+    const int64_t slot[4] = {2, 0, length, 0};   // a layout slot that says equal lengths, the first two offsets
     if (e == hipSuccess) e = hipMemcpy(d_bytes, B.bytes.data(), (size_t)(n * length), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(d_slot, slot, sizeof(slot), hipMemcpyHostToDevice);
     std::vector<uint8_t> out((size_t)n);
@@ -2529,27 +2529,36 @@ int jit_selfcheck(const Program& P, JitKernel* K, hipFunction_t* const* staged, 
             }
         }
     }
-    // the span form, on the batch as fixed-length strings, both results (no
-    // tables yet: a thread that would need them is reported, and not checked)
+    // the span form, on the batch as fixed-length strings, both results
+    uint8_t* d_tables = nullptr;
+    if (!rc && K->spans)
+        if (hipMalloc(&d_tables, P.blob.size()) != hipSuccess ||
+            hipMemcpy(d_tables, P.blob.data(), P.blob.size(), hipMemcpyHostToDevice) != hipSuccess)
+            rc = -1;
     for (int kind = 0; kind < 2 && !rc && K->spans; ++kind) {
         SpanTextArg x;
         x.bytes = d_bytes;
         x.stride = length;
         x.n = n;
         (kind ? (void*&)x.first : (void*&)x.out) = kind ? (void*)d_first : (void*)d_out;
-        x.undone = d_slot + 3;
+        x.first_row = reinterpret_cast<const uint32_t*>(d_tables + P.layout.first);
+        x.follow = reinterpret_cast<const uint32_t*>(d_tables + P.layout.follow);
+        x.bytemask = reinterpret_cast<const uint32_t*>(d_tables + P.layout.bytemask);
+        x.prefix = P.span_prefix;
         void* args[] = {&x};
-        int64_t undone = 0;
         hipError_t r = hipMemsetAsync(kind ? (void*)d_first : (void*)d_out, kind ? 0xff : 0, kind ? 8 * (size_t)n : (size_t)n, st);
-        if (r == hipSuccess) r = hipMemsetAsync(d_slot + 3, 0, 8, st);
         if (r == hipSuccess) r = hipModuleLaunchKernel(K->spans, 64, 1, 1, 64, 1, 1, kSpanLds, st, args, nullptr);
         if (r == hipSuccess) r = hipStreamSynchronize(st);
-        if (r == hipSuccess) r = hipMemcpy(&undone, d_slot + 3, 8, hipMemcpyDeviceToHost);
         if (r == hipSuccess && !kind) r = hipMemcpy(out.data(), d_out, (size_t)n, hipMemcpyDeviceToHost);
         if (r == hipSuccess && kind) r = hipMemcpy(fp.data(), d_first, 8 * (size_t)n, hipMemcpyDeviceToHost);
-        if (r != hipSuccess) rc = -1;
-        else if (!undone && (kind ? fp != B.first : out != B.accept)) K->spans = nullptr;
+        if (r != hipSuccess) {
+            rc = -1;
+        } else if (kind ? fp != B.first : out != B.accept) {
+            K->spans = nullptr;
+            K->selfcheck_dropped |= 1 << kSpanCheckBit;
+        }
     }
+    if (d_tables) (void)hipFree(d_tables);
     if (d_bytes) (void)hipFree(d_bytes);
     if (d_out) (void)hipFree(d_out);
     if (d_first) (void)hipFree(d_first);

@@ -128,6 +128,12 @@ static inline T atomicOr(T* p, T v) {
     return o;
 }
 template <class T>
+static inline T atomicAdd(T* p, T v) {
+    const T o = *p;
+    *p += v;
+    return o;
+}
+template <class T>
 static inline T atomicMin(T* p, T v) {
     const T o = *p;
     if (v < o) *p = v;
