@@ -1727,10 +1727,14 @@ __device__ i64 rx_lower_bound(const i64* offsets, i64 n, i64 v, int lane) {
     return lo + __popcll(__ballot(i < hi && offsets[i] < v));
 }
 
-__device__ __forceinline__ void rx_span_accept(const rx_span_text& X, i64 string, i64 at) {
+// (crowded: fewer strings than regions.  Atomics on one word take their turn,
+// so there none is made that cannot lower the minimum.)
+__device__ __forceinline__ void rx_span_accept(const rx_span_text& X, i64 string, i64 at, bool crowded) {
     if (X.first) {
         const i64 lo = X.offsets ? X.offsets[string] : string * X.stride;
-        atomicMin((unsigned long long*)(X.first + string), (unsigned long long)(at + 1 - lo));
+        unsigned long long* p = (unsigned long long*)(X.first + string);
+        const unsigned long long v = (unsigned long long)(at + 1 - lo);
+        if (!crowded || __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > v) atomicMin(p, v);
     } else {
         X.out[string] = 1;
     }
@@ -1774,7 +1778,7 @@ __device__ void rx_span_alone(const rx_span_text& X, i64 string, i64 from, i64 s
         }
         if ((V[RX_W - 1] >> (RX_ACCEPT & 31)) & 1u) return;   // a later slot has the string's accept
         if ((A[RX_W - 1] >> (RX_ACCEPT & 31)) & 1u) {
-            rx_span_accept(X, string, at);
+            rx_span_accept(X, string, at, false);
             return;
         }
         u32 left = 0u;
@@ -1800,6 +1804,7 @@ extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1
     if (oN <= o0) return;
     const int skew = (int)((unsigned long long)(X.bytes + o0) & 15ull);
     const i64 regions = (oN - o0 + skew + RX_REGION - 1) / RX_REGION;
+    const bool crowded = X.n < regions;
     const i64 per = (regions + gridDim.x - 1) / gridDim.x, r0 = blockIdx.x * per;
     const i64 r1 = r0 + per < regions ? r0 + per : regions;
     if (r0 >= r1) return;
@@ -2031,7 +2036,7 @@ extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1
                 while (b) {
                     const int j = __builtin_ctz(b);
                     b &= b - 1;
-                    rx_span_accept(X, string_of(j, 15), S + (32 * lane + j) * 16 + 16 + u);
+                    rx_span_accept(X, string_of(j, 15), S + (32 * lane + j) * 16 + 16 + u, false);
                 }
             } else {
                 late |= b;
@@ -2041,7 +2046,7 @@ extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1
         while (late) {
             const int j = __builtin_ctz(late);
             late &= late - 1;
-            rx_span_accept(X, string_of(j, 15), 0);
+            rx_span_accept(X, string_of(j, 15), 0, false);
         }
         // A string that the slot before has accepted needs no second note (texts
         // that match everywhere would note every slot).  Only where half of the
@@ -2067,7 +2072,7 @@ extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1
             if (f & (f - 1)) ri[t * 64 + lane] = f & (f - 1);
             else any &= any - 1;
             const i64 at = S + (32 * lane + j) * 16 + t;
-            if (at >= o0 && at < oN) rx_span_accept(X, string_of(j, t), at);
+            if (at >= o0 && at < oN) rx_span_accept(X, string_of(j, t), at, crowded);
         }
         sid = next;
     }

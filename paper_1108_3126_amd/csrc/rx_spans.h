@@ -181,11 +181,15 @@ __device__ __forceinline__ int64_t span_string(const SpanText& X, const SpanStar
     return S.sid - 1 + lo;
 }
 
+// (crowded: many lanes to a string.  Atomics on one word take their turn, 23 ns
+// each, so one that cannot lower the minimum is not made there.)
 template <bool FIRST>
-__device__ __forceinline__ void span_accept(const SpanText& X, const SpanOut& O, int64_t string, int64_t at) {
+__device__ __forceinline__ void span_accept(const SpanText& X, const SpanOut& O, int64_t string, int64_t at, bool crowded) {
     if constexpr (FIRST) {
         const int64_t lo = X.offsets ? X.offsets[string] : string * X.stride;
-        atomicMin(reinterpret_cast<unsigned long long*>(O.first_pos + string), (unsigned long long)(at + 1 - lo));
+        unsigned long long* p = reinterpret_cast<unsigned long long*>(O.first_pos + string);
+        const unsigned long long v = (unsigned long long)(at + 1 - lo);
+        if (!crowded || __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > v) atomicMin(p, v);
     } else {
         O.out[string] = 1;
     }
@@ -209,6 +213,7 @@ __device__ __forceinline__ void span_regions(const SpanProg& P, const SpanText& 
     uint32_t fst[W];   // the threads that the next lane starts, and accept never among them (not nullable)
 #pragma unroll
     for (int w = 0; w < W; ++w) fst[w] = P.first[w];
+    const bool crowded = oN - o0 >= 192 * X.n;
     SpanStarts S;
     S.sid = -1;
     S.list = list;
@@ -353,7 +358,7 @@ __device__ __forceinline__ void span_regions(const SpanProg& P, const SpanText& 
                 }
             }
             if (over >= 0) {
-                span_accept<FIRST>(X, O, span_string(X, S, p0 + B - 1), over);
+                span_accept<FIRST>(X, O, span_string(X, S, p0 + B - 1), over, crowded);
             } else if (span_any<W>(A)) {
                 // Still going (no string began since): up to the string's
                 // end, beside the threads that the next lanes start from here
@@ -389,7 +394,7 @@ __device__ __forceinline__ void span_regions(const SpanProg& P, const SpanText& 
                         if (V[W - 1] & abit) {
                             done = true;   // a later lane has the string's accept, here or before
                         } else if (A[W - 1] & abit) {
-                            span_accept<FIRST>(X, O, string, at + b);
+                            span_accept<FIRST>(X, O, string, at + b, crowded);
                             done = true;
                         } else {
                             uint32_t rest = 0u;
@@ -401,10 +406,23 @@ __device__ __forceinline__ void span_regions(const SpanProg& P, const SpanText& 
                 }
                 if (!done && stop < end) *O.undone = 1;
             }
+            if (FIRST && crowded) {
+                // a lane's first accept counts for nothing where a lane before it has one in the same string
+                const uint64_t with = __ballot(ev != 0u);
+                int64_t s1 = -1, s2 = -1;   // the strings of its first and its last
+                if (ev) {
+                    s1 = span_string(X, S, p0 + __builtin_ctzll(ev));
+                    s2 = ev & (ev - 1) ? span_string(X, S, p0 + 63 - __builtin_clzll(ev)) : s1;
+                }
+                const int lane = tid & 63;
+                const uint64_t lower = with & ((1ull << lane) - 1);
+                const int64_t before = __shfl(s2, lower ? 63 - __builtin_clzll(lower) : lane, 64);
+                if (lower && before == s1) ev &= ev - 1;
+            }
             while (ev) {
                 const int k = __builtin_ctzll(ev);
                 ev &= ev - 1;
-                span_accept<FIRST>(X, O, span_string(X, S, p0 + k), S.start + p0 + k);
+                span_accept<FIRST>(X, O, span_string(X, S, p0 + k), S.start + p0 + k, crowded);
             }
         }
     }
