@@ -258,3 +258,38 @@ def test_one_long_string(edits):
             assert bool(undone) == lives
             if not undone:
                 np.testing.assert_array_equal(got, expect, err_msg=kind)
+
+
+@pytest.mark.parametrize("share", [0.0, 0.02, 0.2, 1.0])
+@pytest.mark.parametrize("pattern", [b"a[^q]*b", b"a.*b.*c.*d", b"a{2}[^q]{70}[^q]*b", b"a[^q]{40}[^q]*b.{60}c"], ids=str)
+def test_few_and_many_threads_that_live_on(pattern, share):
+    """Threads that live to their string's end: none, fewer than a workgroup's list holds over its regions, more; sets
+    of one to four words and of five (those that are not looked at for standing still)."""
+    p, tree = _program(pattern)
+    rng = np.random.default_rng([len(pattern), int(100 * share)])
+    lens = np.concatenate([rng.integers(100, 400, 60), [5000, 0, 3, 2000]])
+    offs = np.zeros(len(lens) + 1, np.int64)
+    np.cumsum(lens, out=offs[1:])
+    data = np.frombuffer(b"xyzxyzbcdd", np.uint8)[rng.integers(0, 10, int(offs[-1]))].copy()
+    data[data == ord("b")] = np.where(rng.random(int((data == ord("b")).sum())) < 0.05, ord("b"), ord("x"))
+    for i in np.nonzero(rng.random(len(lens)) < share)[0]:
+        if lens[i] > 20:
+            data[offs[i] + 10:offs[i] + 12] = ord("a")
+    want_first, want = earliest(tree, data, offs)
+    for B, grid in ((16, 1), (16, 3), (64, 1)):
+        for first, expect in ((False, want), (True, want_first)):
+            got, _ = run("table", p, data, offs, first=first, skew=5, grid=grid, B=B)
+            np.testing.assert_array_equal(got, expect, err_msg=f"B {B} grid {grid} first {first}")
+
+
+def test_programs_whose_threads_may_live_on():
+    """Five-word sets among them; the oracle on a handful of strings."""
+    p, tree = _program(b"a[^q]{150}[^q]*b|cde")
+    assert p.info.words >= 5
+    rng = np.random.default_rng(5)
+    data = np.frombuffer(b"xyzab", np.uint8)[rng.integers(0, 5, 6000)].copy()
+    offs = np.array([0, 3000, 3000, 3100, 5900, 6000], np.int64)
+    want_first, want = earliest(tree, data, offs)
+    for first, expect in ((False, want), (True, want_first)):
+        got, _ = run("table", p, data, offs, first=first, B=16)
+        np.testing.assert_array_equal(got, expect)
