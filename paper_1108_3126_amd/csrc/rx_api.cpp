@@ -193,8 +193,13 @@ int64_t next_slot_id() {
 // with a lane each, in one launch instead of two: 50,000 of 10 bytes 11.5
 // against 14.8 us, of 21 bytes 16.2 against 15.8 us, 2 * 10^6 of 10 bytes 62
 // against 43 us.
+// A lane per string takes about 0.17 us a byte of the longest, and a thread
+// that lives on past its span 0.19: below 512 bytes, programs whose threads may
+// (see circuit_spans) keep it (200,000 strings of 256 bytes, err.*timeout, 73
+// us, 165 over spans).
 bool spans_ok(const Program* P, const LaunchArgs& a) {
     if (P->span_prefix < 0 || a.block != 0 || a.grid != 0 || a.unroll != 0) return false;
+    if (!a.offsets && P->span_lives && a.stride < 512) return false;
     return a.offsets || a.stride >= 20 || a.n >= ((int64_t)2 << 20) / (a.stride + 1);
 }
 // Spans over the compiled circuit or over the tables.  A circuit's wavefront
@@ -205,8 +210,12 @@ bool spans_ok(const Program* P, const LaunchArgs& a) {
 // 50,000 lines 25 (tables), 100,000 26 (circuit) and 37, 10^6 97 and 230;
 // five words, 50,000 lines 33 (tables), 100,000 20 and 50.  With offsets the
 // bytes are not known on the host, so the strings' number stands for them.
+// A thread that lives on makes the circuit take its whole region through every
+// byte of it, and the tables one lane: programs of one or two words where that
+// can be told (err.*timeout) take the tables, 10^6 lines with err in 5% of them
+// 1,030 us (tables) and 1,890 (circuit).
 bool circuit_spans(const Program* P, const LaunchArgs& a) {
-    if (!jit_spans_ready(P)) return false;
+    if (!jit_spans_ready(P) || P->span_lives) return false;
     const bool narrow = P->W <= 2;
     if (a.offsets) return a.n >= (narrow ? 100000 : 40000);
     return (double)a.n * (double)a.stride >= (narrow ? 12e6 : 5e6);
@@ -219,10 +228,12 @@ bool circuit_spans(const Program* P, const LaunchArgs& a) {
 // (spans) and 72 us (sliced), 500,000 58 and 76, 800,000 91 and 91; of 64
 // bytes: 250,000 20 and 27; of 16 bytes: 19 and 18.  A circuit whose staged
 // kernels would spill (55 words: 800,000 strings 142 and 197 us) takes spans
-// for any number.
+// for any number.  Programs whose threads may live on (see circuit_spans) stay
+// with the sliced kernel, whose time is the same for every text: 200,000
+// strings of 256 bytes, err.*timeout, 67 us, 150 over spans.
 constexpr int64_t kSlicedStrings = 512 * 1024;
 bool spans_over_sliced(const Program* P, const LaunchArgs& a) {
-    if (!spans_ok(P, a) || a.stride < 64) return false;
+    if (!spans_ok(P, a) || a.stride < 64 || P->span_lives) return false;
     if (!jit_spans_ready(P)) return (double)a.n * (double)a.stride < 8e6 && a.n < kSlicedStrings;
     return a.n < kSlicedStrings || jit_default_staging(P) != 5;
 }
@@ -255,7 +266,7 @@ int rx_match_ex(const rx_program* prog, const uint8_t* d_bytes, const int64_t* d
         if (int e = launch_spans_fill(a)) return hip_fail(e, "kernel launch (fill)");
     // (over spans, equal lengths are worth the check only from where the
     // bit-sliced kernel is the faster one)
-    const int64_t check_from = spans && jit_spans_ready(P) ? kSlicedStrings : kLayoutMinStrings;
+    const int64_t check_from = spans && jit_spans_ready(P) && !P->span_lives ? kSlicedStrings : kLayoutMinStrings;
     if (variant == RX_VARIANT_AUTO && n >= check_from && jit_offsets_ready(P)) {
         // Equal-length consecutive strings go to the bit-sliced kernel: a
         // check on the device fills this call's layout slot, the sliced kernel

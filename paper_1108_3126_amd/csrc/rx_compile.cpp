@@ -323,6 +323,24 @@ int compile(const rx_ast_node* ast, int32_t n_ast, int32_t root, const rx_class*
         for (int32_t r = 0; r < L && ok; ++r)
             ok = r == pre || !((P->follow[(size_t)r * W + (pre >> 5)] >> (pre & 31)) & 1u);
         if (ok) P->span_prefix = pre;
+        if (ok && W <= 2) {
+            // Leaves that at least 72 of the 95 printable bytes keep (a dot, a
+            // negated class), but for First's (every byte starts those anew) and
+            // those that accept (the search suffix): reach[r] is what they lead
+            // to among themselves, a cycle a leaf that leads to itself.
+            std::vector<uint64_t> reach((size_t)L, 0);
+            for (int32_t r = 0; r < L; ++r) {
+                int kept = 0;
+                for (int c = 0x20; c < 0x7f; ++c) kept += (P->bytemask[(size_t)c * W + (r >> 5)] >> (r & 31)) & 1u;
+                const bool accepts = (P->follow[(size_t)r * W + (L >> 5)] >> (L & 31)) & 1u;
+                if (kept < 72 || accepts || ((P->first[(size_t)(r >> 5)] >> (r & 31)) & 1u)) continue;
+                reach[(size_t)r] = P->follow[(size_t)r * W] | (W > 1 ? (uint64_t)P->follow[(size_t)r * W + 1] << 32 : 0);
+            }
+            for (int32_t k = 0; k < L; ++k)
+                for (int32_t r = 0; r < L; ++r)
+                    if ((reach[(size_t)r] >> k) & 1u) reach[(size_t)r] |= reach[(size_t)k];
+            for (int32_t r = 0; r < L; ++r) P->span_lives |= (reach[(size_t)r] >> r) & 1u;
+        }
     }
 
     // device image

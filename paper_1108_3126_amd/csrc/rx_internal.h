@@ -42,6 +42,9 @@ struct Program {
     // rank of the search prefix's any-byte leaf, for a searched program that
     // runs over equal spans of bytes (rx_spans.h); -1: it does not
     int32_t span_prefix = -1;
+    // of those, a program of at most two words whose threads may live on: once
+    // past First, there is a cycle of leaves that nearly every byte keeps
+    bool span_lives = false;
     std::vector<int32_t> leaf_node;  // rank -> node
     std::vector<int32_t> leaf_rank;  // node -> rank, -1 for internal nodes
     // evolution tables (Def. 5.1), 32-bit words

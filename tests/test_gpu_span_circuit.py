@@ -105,3 +105,25 @@ def test_one_long_string(pattern, edits):
     print(pattern, edits, end, flush=True)
     assert int(rx.match_long(p, d).item()) == want[0]
     assert int(rx.match_first_long(p, d).item()) == end
+
+
+@pytest.mark.parametrize("jit", [False, True])
+@pytest.mark.parametrize("length,base", [(64, 4000), (256, 2000), (100, 3000), (511, 1000), (512, 1000), (1040, 500)])
+def test_programs_whose_threads_may_live_on(length, base, jit):
+    """err.*timeout and the like: equal lengths stay with the kernels that one such thread does not slow down."""
+    tree = rx.parse(b"a[^q]*b|cde")
+    p = rx.compile(*tree, search=True).upload()
+    if jit:
+        p.jit()
+    rng = np.random.default_rng(length)
+    data, offs = _strings(b"a[^q]*b|cde", rng, np.full(base, length))
+    want_first, want = earliest(tree, data, offs)
+    assert 0 < want.sum() < base
+    times = -(-20_000 // base)
+    d, o = _tiled(data, offs, times, 0)
+    d, o = torch.from_numpy(d).cuda(), torch.from_numpy(o).cuda()
+    print(length, base * times, jit, flush=True)
+    _compare(rx.match(p, d, o), want, times, "match")
+    _compare(rx.match_first(p, d, o), want_first, times, "first")
+    _compare(rx.match_fixed(p, d, length, base * times), want, times, "fixed")
+    _compare(rx.match_first_fixed(p, d, length, base * times), want_first, times, "first fixed")
