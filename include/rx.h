@@ -307,9 +307,10 @@ int rx_match_first_fixed(const rx_program* prog, const uint8_t* d_bytes, int64_t
  * segments' maps.
  * With chunks = 0, a searched program that does not match the empty string (a set of
  * at most 16 words) and a string of 4,096 bytes or more, spans of the string
- * run first, as in rx_match; only if a thread outlives its span by more than
- * 4,096 bytes (or the circuit's region), which the device finds, do the kernels
- * above run too (they are queued either way, and return at once; the
+ * run first, as in rx_match (not before circuit chunks of at most four words,
+ * or of a program whose threads may live on, which take as long at most); only
+ * if a thread outlives its span by about 160 bytes (48 in the circuit), which
+ * the device finds, do the kernels above run too (they are queued either way, and return at once; the
  * device's finding is kept in the workspace, behind what they use, and where
  * the default count of chunks leaves no room for it there is one chunk fewer; a
  * workspace that still has none runs them alone).

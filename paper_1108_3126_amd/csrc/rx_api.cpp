@@ -417,6 +417,16 @@ int long_spans(const Program* P, const uint8_t* d_bytes, int64_t length, int32_t
     return RX_OK;
 }
 
+// Circuit chunks take a run per word and one more, whatever the text: 8 MiB 23
+// us (two words), 30 (three), 69 (err.*timeout, ten), 147 (seventeen).  Spans
+// take 19, and where a thread lives on 25 to 45 before the chunks begin: they go
+// first where they save more than that.
+bool long_spans_first(const Program* P) {
+    int ns = 0;
+    jit_ready(P, &ns, nullptr);
+    return ns > 4 && !P->span_lives;
+}
+
 int check_long_args(const Program* P, const uint8_t* d_bytes, int64_t length, int32_t chunks, const void* d_out) {
     if (!P) return fail(RX_EINVAL, "program is NULL");
     if (length < 0 || chunks < 0) return fail(RX_EINVAL, "negative length or chunk count");
@@ -439,9 +449,10 @@ int rx_match_long(const rx_program* prog, const uint8_t* d_bytes, int64_t length
     const int64_t circuit_need = chunks == 0 && length <= (int64_t(1) << 40) ? long_chunk_work_bytes(P, length) : -1;
     LongGate gate;
     if (circuit_need >= 0 && (size_t)circuit_need <= work_bytes) {
-        if (int rc = long_spans(P, d_bytes, length, chunks, d_work, (size_t)circuit_need, work_bytes, d_out, nullptr, &gate,
-                                stream))
-            return rc;
+        if (long_spans_first(P))
+            if (int rc = long_spans(P, d_bytes, length, chunks, d_work, (size_t)circuit_need, work_bytes, d_out, nullptr, &gate,
+                                    stream))
+                return rc;
         if (int e = launch_long_chunks(P, d_bytes, length, d_work, d_out, gate, stream)) return hip_fail(e, "kernel launch");
         return RX_OK;
     }

@@ -245,7 +245,7 @@ struct LongGate {
     const int64_t* slot = nullptr;
     int64_t id = 0;
 };
-constexpr int64_t kSpanLongLimit = 4096;
+constexpr int64_t kSpanLongLimit = 128;
 constexpr size_t kLongGateBytes = 16;   // a word at an 8-byte boundary
 int launch_span_long_begin(const LongGate& gate, uint8_t* out, int64_t* first, void* stream);
 // Equal-length consecutive strings for rx_match (rx_kernels.hip): the slot of

@@ -1709,7 +1709,8 @@ struct rx_span_text {
     int prefix;
     const i64* skip;      // rx_match's layout slot: nothing to do when it holds 2 * skip_id
     i64 skip_id;
-    i64* undone;          // not NULL: set, instead of following a thread past the last lane
+    i64* undone;          // not NULL: set, instead of following a thread that
+                          // outlives its slot by 48 bytes
 };
 
 // The first i in [0, n] with offsets[i] >= v, or n + 1.
@@ -1979,12 +1980,13 @@ extern "C" __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1
             }
             return lo;
         };
+        const int past = X.undone ? 48 : 31 * 16;   // 31 slots: the region's last lane
         // (a position's words are read while the one before runs)
         u32 ml = mk[lane], mu = mk[up];
         rx_v4 lo = pl[lane], hi = pl[64 + lane], lu = pl[up], hu = pl[64 + up];
         for (int u = 0; __ballot(left != 0u) != 0ull; ++u) {
             if ((u & 15) == 0) {
-                if (u == 31 * 16) {   // past the last lane: in table form, or not at all
+                if (u == past) {   // in table form, or not at all
                     if (X.undone) {
                         if (left) *X.undone = 1;
                     } else {

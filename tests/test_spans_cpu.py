@@ -260,6 +260,16 @@ def test_one_long_string(edits):
                 np.testing.assert_array_equal(got, expect, err_msg=kind)
 
 
+def test_one_long_string_is_given_up_early():
+    """The kernels that follow are the faster ones where threads live on: the circuit does not run its whole region."""
+    p, tree = _program(b"a[^q]*b|cde")
+    for gap, gives_up in ((20, False), (100, True)):
+        text = np.full(40_000, ord("x"), np.uint8)
+        text[20_000], text[20_000 + gap] = ord("a"), ord("q")
+        got, undone = run("circuit", p, text, stride=text.size, n=1, limit=128)
+        assert bool(undone) == gives_up and got[0] == 0
+
+
 @pytest.mark.parametrize("share", [0.0, 0.02, 0.2, 1.0])
 @pytest.mark.parametrize("pattern", [b"a[^q]*b", b"a.*b.*c.*d", b"a{2}[^q]{70}[^q]*b", b"a[^q]{40}[^q]*b.{60}c"], ids=str)
 def test_few_and_many_threads_that_live_on(pattern, share):
