@@ -235,7 +235,7 @@ int launch_spans_fill(const LaunchArgs& a);
 int launch_spans(const LaunchArgs& a);
 // One long string over spans, before the chunk-parallel kernels: a word in
 // memory that belongs to the call (its workspace), 2 * id; a thread that
-// outlives its span by more than kSpanLongLimit bytes (or a circuit's region)
+// outlives its span by more than kSpanLongLimit bytes (48 in a circuit)
 // sets it to 1 instead of being followed.  The chunk-parallel kernels given the
 // gate do nothing where it holds 2 * id still.  They are two, and a second that
 // ran after a first that did not would compose what nobody wrote: so no other

@@ -47,8 +47,10 @@ struct SpanOut {
 
 constexpr int kSpanMax = 64;    // bytes per lane and turn: 16, 32 or 64
 constexpr int kSpanTail = 32;   // bytes past its span that a lane reads from the staged text
-constexpr int kSpanList = 448;  // string starts of a region kept in LDS
-constexpr int kSpanPend = 192;  // words for the threads that outlive the staged text (see span_regions)
+// (512 together: more, and sets of three words have room for four workgroups in
+// a compute unit instead of five, whose LDS goes by 1,280 bytes; 100,000 lines 41 -> 55 us)
+constexpr int kSpanList = 416;  // string starts of a region kept in LDS
+constexpr int kSpanPend = 96;   // words for the threads that outlive the staged text (see span_regions)
 
 // LDS words per table row: rows of more than two words in whole 16-byte reads
 constexpr int span_row_words(int W) { return W <= 2 ? W : (W + 3) / 4 * 4; }
@@ -214,10 +216,18 @@ __device__ __forceinline__ void span_regions(const SpanProg& P, const SpanText& 
     uint32_t fst[W];   // the threads that the next lane starts, and accept never among them (not nullable)
 #pragma unroll
     for (int w = 0; w < W; ++w) fst[w] = P.first[w];
+    // kStill: where a thread goes on past the staged text, in sets of one or
+    // two words: a byte that leaves the threads as they were is the rule there
+    // (x.*y between its ends), and a step is a chain of LDS reads.  What it does
+    // depends on the leaves of A and V that survive the byte and on the row of
+    // N: where the survivors are those of a step that changed nothing, and N's
+    // row adds nothing to V, neither does this one.  (Wider sets seldom stand
+    // still: three words, random text, 38 us without, 41 with.)
+    constexpr bool kStill = W <= 2;
     uint32_t* pend = list + kSpanList;   // how many, then {at, string, threads} each
     constexpr int kPendWords = W + 4, kPendMax = (kSpanPend - 1) / kPendWords;
     if (tid == 0) pend[0] = 0u;
-    const bool crowded = oN - o0 >= 192 * X.n;
+    const bool crowded = oN - o0 >= 4096 * X.n;   // (from 192 on, lines of 320 bytes lost 8%)
     SpanStarts S;
     S.sid = -1;
     S.list = list;
@@ -230,8 +240,8 @@ __device__ __forceinline__ void span_regions(const SpanProg& P, const SpanText& 
         int64_t from = 0, string = -1;   // where A goes on past the staged text, in which string (-1: it does not)
         __syncthreads();                 // the last region's text and starts have been read
         if (r == r1) {
-            // (over all wavefronts, since lanes that stand still wait for those of theirs that do not)
-            const int k = (tid & 63) * (T / 64) + (tid >> 6);
+            // (over all wavefronts where lanes that stand still wait for those of theirs that do not, else in few)
+            const int k = kStill ? (tid & 63) * (T / 64) + (tid >> 6) : tid;
             if (k < (int)pend[0]) {
                 const uint32_t* e = pend + 1 + k * kPendWords;
                 from = (int64_t)((uint64_t)e[1] << 32 | e[0]);
@@ -431,16 +441,7 @@ __device__ __forceinline__ void span_regions(const SpanProg& P, const SpanText& 
             // (16-byte aligned; the next 16 bytes are on their way)
             uint4 nx = make_uint4(0u, 0u, 0u, 0u);
             if (from < stop) nx = *reinterpret_cast<const uint4*>(X.bytes + from);
-            // In sets of up to four words: a byte that leaves the threads as
-            // they were is the rule here (x.*y between its ends), and a step is
-            // a chain of LDS reads.  What it does depends on the leaves of A
-            // and V that survive the byte and on the row of N: where the
-            // survivors are those of a step that changed nothing, and N's row
-            // adds nothing to V, neither does this one.  (Wider sets seldom
-            // stand still, and keeping two more of them costs the kernel its
-            // wavefronts.)
-            constexpr bool kStill = W <= 4;
-            constexpr int kAhead = W == 1 ? FIRST ? 2 : 4 : 1;   // bytes looked at together
+            constexpr int kAhead = W == 1 && !FIRST ? 4 : 1;   // bytes looked at together
             bool still = false;
             uint32_t fy[W] = {}, fz[W] = {};
             for (int64_t at = from; at < stop && !done; at += 16) {

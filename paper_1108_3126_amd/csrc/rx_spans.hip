@@ -26,8 +26,9 @@ __global__ __launch_bounds__(256) void k_fill(V* __restrict__ out, int64_t n, V 
         out[i] = v;
 }
 
+// (as many wavefronts per SIMD as the LDS of narrow sets lets in)
 template <int W, int T, bool FIRST>
-__global__ __launch_bounds__(T) void k_spans(SpanArgs a) {
+__global__ __launch_bounds__(T, W <= 2 ? 6 : W <= 4 ? 5 : 1) void k_spans(SpanArgs a) {
     extern __shared__ __align__(16) uint32_t lds[];
     constexpr int WP = span_row_words(W);
     if (a.skip && __hip_atomic_load(a.skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 2 * a.skip_id) return;
