@@ -199,7 +199,8 @@ int rx_program_upload(rx_program* prog, void* d_buf, size_t cap, void* stream);
  * begin in its span, so neither a long string nor uneven ones leave lanes
  * idle.  With a compiled circuit of at most 64 words (rx_program_jit) and
  * enough strings, the circuit runs over spans of 16 bytes instead, 2,048 of
- * them to a wavefront.  The others: wavefronts per string for sets above 16 words, and
+ * them to a wavefront (not for programs of one or two words whose threads may
+ * live on, such as err.*timeout).  The others: wavefronts per string for sets above 16 words, and
  * for sets of 6-16 words when the strings number at most four per SIMD
  * (16 x compute units); otherwise one lane per string.  When the program's bit-sliced circuit is compiled
  * (rx_program_jit) and n >= 16384 (524288 where the circuit runs over spans), a check on the device decides whether the
@@ -257,9 +258,9 @@ typedef struct {
  * it, the length of the shortest prefix in the language (k = len_i is a
  * whole-string match only when no shorter prefix matched).  Strings and
  * offsets as for rx_match; d_first is int64[n] on the device.  Runs the
- * table-form kernels (a searched program over spans as in rx_match, else one
- * lane per string up to 16 words, else one wavefront per string), stopping
- * each string at its first accept.  Errors
+ * table-form kernels (a searched program over spans as in rx_match, which read
+ * every byte; else one lane per string up to 16 words, else one wavefront per
+ * string, stopping each string at its first accept).  Errors
  * as rx_match. */
 int rx_match_first(const rx_program* prog, const uint8_t* d_bytes, const int64_t* d_offsets, int64_t n,
                    int64_t* d_first, void* stream);
@@ -385,7 +386,8 @@ int rx_match_ex(const rx_program* prog, const uint8_t* d_bytes, const int64_t* d
  * otherwise the table-form kernels run.  A searched program's strings run over
  * spans, as in rx_match, where that is faster: lengths and addresses that the
  * sliced kernel does not take, and strings of 64 bytes or more that are fewer
- * than 524288 or whose circuit fits no staged kernel.  Same results either way.
+ * than 524288 or whose circuit fits no staged kernel (programs whose threads may
+ * live on: only from 512 bytes on, and without a circuit).  Same results either way.
  * Errors: RX_EINVAL, RX_ENOTUPLOADED, RX_EHIP.
  */
 int rx_match_fixed(const rx_program* prog, const uint8_t* d_bytes, int64_t length, int64_t n, uint8_t* d_out,

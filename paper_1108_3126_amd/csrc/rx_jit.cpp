@@ -1673,8 +1673,9 @@ extern "C" __global__ __launch_bounds__(64 * RX_SPEC_WAVES) void rx_planes_spec(
 //
 // 16 bytes a slot: their planes (32 KB) and two words per position beside them
 // are a quarter of a compute unit's LDS, so every SIMD has a wavefront; what is
-// left past a slot lives five bytes or so in the longest of 2,016 slots, so
-// about a third more steps than bytes.  One wavefront per SIMD leaves it room
+// left past a slot lives five bytes or so in the longest of 2,016 slots (43
+// words, lines of 120 bytes), so about a third more steps than bytes; one thread
+// that lives on takes the region through up to 496 positions.  One wavefront per SIMD leaves it room
 // for the next region's bytes in registers (128 of them).  10^6 lines (120
 // MB), 43 words: 87 us for the kernel, 57% of it vector instructions (6,300
 // a region: 1,280 for the transposes, 170 a position), a fourth waiting (the
