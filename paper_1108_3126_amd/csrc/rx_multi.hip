@@ -281,7 +281,9 @@ int span_queue_shape(const ProgDesc* progs, int n, int widest, SpanQueueShape* s
     if (hip_cu_count(&cus) || cus <= 0) cus = 256;
     int per = (160 * 1024) / (s->lds + 512);
     s->grid = cus * (per < 1 ? 1 : per > 8 ? 8 : per);
-    return s->lds > 64 * 1024 ? (int)hipFuncSetAttribute(s->kernel, hipFuncAttributeMaxDynamicSharedMemorySize, s->lds) : 0;
+    // (the widest program's size: another thread's call must not lower it before the launch)
+    constexpr int kMost = 4 * span_lds_words(kLaneMaxWords, 32 * kLaneMaxWords, kSpanQueueThreads);
+    return s->lds > 64 * 1024 ? (int)hipFuncSetAttribute(s->kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kMost) : 0;
 }
 
 // -- bucketing -------------------------------------------------------------

@@ -52,9 +52,9 @@ template <int W, bool FIRST>
 int launch_spans_w(const LaunchArgs& a, const SpanArgs& k, int cus) {
     constexpr int T = span_threads(W);
     const int lds = 4 * span_lds_words(W, a.L, T);
-    if (lds > 64 * 1024)
-        if (hipError_t e = hipFuncSetAttribute((const void*)k_spans<W, T, FIRST>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, lds))
+    if (lds > 64 * 1024)   // (the widest program's size: another thread's call must not lower it before the launch)
+        if (hipError_t e = hipFuncSetAttribute((const void*)k_spans<W, T, FIRST>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               4 * span_lds_words(W, 32 * W, T)))
             return (int)e;
     int per_cu = (160 * 1024) / (lds + 256);
     if (per_cu > 2048 / T) per_cu = 2048 / T;
